@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "iso_device.h"
@@ -1014,7 +1015,7 @@ __global__ void __launch_bounds__(1024) k_normalize_cols(double* __restrict__ L,
 unsigned grid_for(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 4096)); }
 
 
-constexpr int GT = 64, GK = 16;
+constexpr int GK = 16;
 
 }  // namespace
 }  // namespace iso
@@ -1024,9 +1025,10 @@ namespace {
 
 // A batch of independent GEMMs in one launch: grid.z indexes the job; blocks outside a
 // job's M x N exit.  C(i,j) = alpha * sum_k A(i,k) B(k,j) + beta * C(i,j) with X(i,k) at
-// X[i*xs0 + k*xs1].  `upper`: only the tiles on or above the diagonal are computed (for a
-// symmetric product whose lower triangle the caller fills in).  `skip`: if set and *skip is
-// nonzero when the kernel runs, the job is left out (an iteration whose job has converged).
+// X[i*xs0 + k*xs1].  `upper`: only the tiles on or above the diagonal are computed, for a
+// symmetric product; 1: the caller fills in the lower triangle where it needs one, 2: a tile above
+// the diagonal is also stored transposed below it.  `skip`: if set and *skip is nonzero when the
+// kernel runs, the job is left out (an iteration whose job has converged).
 struct GemmJob {
   const double* A;
   const double* B;
@@ -1039,99 +1041,152 @@ struct GemmJob {
 };
 
 typedef double gemm_f64x4_t __attribute__((ext_vector_type(4)));
+typedef double gemm_f64x2_t __attribute__((ext_vector_type(2)));
+typedef double gemm_f64x2_u __attribute__((ext_vector_type(2), aligned(8)));   // 16 bytes at 8-byte alignment
 
 // One output tile of C = alpha A B + beta C on v_mfma_f64_16x16x4_f64 (lane (ln, g) supplies
 // A[ln][g] and B[g][ln], receives D[g + 4v][ln] in register pair v).  W MFMA blocks per wave side:
-// the four waves (2 x 2) each own a 16W x 16W block of the 32W x 32W tile; W = 2 gives 64 x 64
-// tiles, W = 4 gives 128 x 128 tiles (16 MFMAs per 4-deep k step per wave, and each k-tile load
-// feeds twice the rows and columns).  k in steps of GK = 16 staged in LDS, double-buffered: the
-// next k-tile is loaded into registers before the current one's MFMAs and written to the other
-// buffer after them, one barrier per step.  Operands are loaded along whichever of their strides
-// is 1, so row- and column-major inputs both read whole cache lines, and staged in the layout that
-// load writes without bank conflicts: k-major ([k][i], rows of PAD doubles, padded so that the four
-// k rows of a fragment read fall on different bank halves) for an operand read along i, i-major
-// ([i][k], rows of SK = GK + 2 doubles) for one read along k.  In the i-major layout the sixteen
-// rows of a fragment read start 36 banks apart (mod 64), so they and the two k of a half-wave
-// cover the 64 banks once; a k-major store of a k-fast operand would put 16 k rows 1152 bytes apart
-// (8-way conflicts).
+// the four waves (2 x 2) each own a 16W x 16W block of the 32W x 32W tile (128, 64 or 32 square).
+//
+// Bound by the matrix cores: an MFMA occupies its SIMD for 64 cycles, so one 16-deep k step of a
+// 128 x 128 tile is 4096 cycles against 32 LDS reads and 8 global loads per lane, and the loop
+// only has to keep the MFMAs back to back.  k steps of GK = 16 are double-buffered in LDS; the next
+// k-tile goes from global memory to registers (16-byte loads) while the current one is multiplied
+// and to LDS before the last quarter of it; the fragments of a quarter are read one quarter ahead
+// of the MFMAs that use them, those of the next k-tile's first quarter under the last quarter's
+// MFMAs: the barrier and the LDS latency are covered by MFMAs already queued.  Measured (one launch;
+// reads, LDS reads and MFMAs of a k step not overlapped -> this loop): 2048^3 46-53 -> 53-58 TFLOP/s
+// (one workgroup per CU), four of them at once 57-59 -> 65, 4096^3 58-60 -> 65-67; a bare MFMA stream
+// reaches 77.  Four 2048^3 Gram products by one triangle and its mirror 1.07 -> 0.82 ms; 256^3 on
+// 32-wide tiles instead of 128-wide ones (64 workgroups, not 4) 50 -> 8 us.
+//
+// Operands are loaded along whichever of their strides is 1, so row- and column-major inputs both
+// read whole cache lines, and staged in the layout that load writes without bank conflicts:
+// k-major ([k][i], rows of PAD doubles) for an operand read along i, i-major ([i][k], rows of
+// SK = GK + 2 doubles) for one read along k; the rows of a fragment read then fall on different
+// banks in either layout.  One of each operand's strides has to be 1.
 template <int W>
 struct GemmTile {
-  static constexpr int TM = 32 * W, TW = 16 * W, PAD = (W == 2) ? 80 : TM + 16, PT = GK * TM / 256;
+  static constexpr int TM = 32 * W, TW = 16 * W, PAD = (W == 2) ? 80 : TM + 16, PT = GK * TM / 512;
   static constexpr int SK = GK + 2;
   static constexpr int BUF = (GK * PAD > TM * SK) ? GK * PAD : TM * SK;
 };
 
-// AK / BK: A / B is read along k, else along its rows / columns; a template parameter, so that
-// each instantiation holds only its own address arithmetic.
-template <int W, bool AK, bool BK>
+// AK / BK: A / B is read along k, else along its rows / columns.  FULL: the tile lies inside the
+// output; otherwise every entry is checked (and loaded by itself).
+template <int W, bool AK, bool BK, bool FULL>
 __device__ __forceinline__ void gemm_tile_l(const GemmJob& J, int64_t i0, int64_t j0, double (*As)[GemmTile<W>::BUF],
                                             double (*Bs)[GemmTile<W>::BUF]) {
   using T = GemmTile<W>;
   constexpr int TM = T::TM, TW = T::TW, PAD = T::PAD, PT = T::PT, SK = T::SK;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g = lane >> 4, ln = lane & 15;
   const int wm = w >> 1, wn = w & 1;
-  constexpr bool a_kfast = AK, b_kfast = BK;
   gemm_f64x4_t acc[W][W];
 #pragma unroll
   for (int rb = 0; rb < W; ++rb)
 #pragma unroll
     for (int cb = 0; cb < W; ++cb) acc[rb][cb] = gemm_f64x4_t{0.0, 0.0, 0.0, 0.0};
-  double pa[PT], pb[PT];
-  // element e of a k-tile: 16 consecutive k of one row (k-fast operand) or TM consecutive rows
-  // of one k (the other)
-  auto load = [&](int64_t k0) {
+  // pair q of this thread: (line, position) of a k-fast operand is (row, k), of the other (k, row)
+  constexpr int LPA = AK ? GK / 2 : TM / 2, LPB = BK ? GK / 2 : TM / 2;    // pairs per line
+  const int la = threadIdx.x / LPA, pa2 = 2 * (threadIdx.x % LPA);
+  const int lb = threadIdx.x / LPB, pb2 = 2 * (threadIdx.x % LPB);
+  const int64_t sa = AK ? J.as0 : J.as1, sb = BK ? J.bs1 : J.bs0;           // stride between lines
+  const double* abase = J.A + i0 * J.as0;
+  const double* bbase = J.B + j0 * J.bs1;
+  gemm_f64x2_t ra[PT], rb2[PT];
+  auto load1 = [&](const double* base, int64_t stride, int64_t k0, int line, int pos, bool kf, int64_t lim) {
+    // one pair with every entry checked; lim: rows (columns) left in the output from this tile
+    gemm_f64x2_t v = {0.0, 0.0};
 #pragma unroll
-    for (int q = 0; q < PT; ++q) {
-      const int e = threadIdx.x + 256 * q;
-      const int ka = a_kfast ? (e & 15) : (e / TM), ia = a_kfast ? (e >> 4) : (e % TM);
-      const int kb = b_kfast ? (e & 15) : (e / TM), jb = b_kfast ? (e >> 4) : (e % TM);
-      const int64_t gi = i0 + ia, gka = k0 + ka, gj = j0 + jb, gkb = k0 + kb;
-      pa[q] = (gi < J.M && gka < J.K) ? gmem(J.A)[gi * J.as0 + gka * J.as1] : 0.0;
-      pb[q] = (gj < J.N && gkb < J.K) ? gmem(J.B)[gkb * J.bs0 + gj * J.bs1] : 0.0;
+    for (int h = 0; h < 2; ++h) {
+      const int64_t k = k0 + (kf ? pos + h : line), i = kf ? line : pos + h;
+      if (k < J.K && i < lim) v[h] = gmem(base)[kf ? i * stride + k : k * stride + i];
+    }
+    return v;
+  };
+  // byte offsets from the tile's uniform base (FULL tiles only: gemm_tile checks that they fit)
+  const uint32_t oa = (uint32_t)(la * sa + pa2) * 8u, ob = (uint32_t)(lb * sb + pb2) * 8u;
+  const uint32_t qa = (uint32_t)((256 / LPA) * sa) * 8u, qb = (uint32_t)((256 / LPB) * sb) * 8u;
+  auto pair_at = [](const double* base, uint32_t off) {
+    return *(const __attribute__((address_space(1))) gemm_f64x2_u*)((const __attribute__((address_space(1))) char*)base + off);
+  };
+  auto load = [&](int64_t k0) {
+    if (FULL && k0 + GK <= J.K) {
+      const double* ap = abase + (AK ? k0 : k0 * J.as1);
+      const double* bp = bbase + (BK ? k0 : k0 * J.bs0);
+#pragma unroll
+      for (int q = 0; q < PT; ++q) {
+        ra[q] = pair_at(ap, oa + q * qa);
+        rb2[q] = pair_at(bp, ob + q * qb);
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < PT; ++q) {
+        ra[q] = load1(abase, sa, k0, la + q * (256 / LPA), pa2, AK, J.M - i0);
+        rb2[q] = load1(bbase, sb, k0, lb + q * (256 / LPB), pb2, BK, J.N - j0);
+      }
     }
   };
   auto store = [&](int buf) {
 #pragma unroll
     for (int q = 0; q < PT; ++q) {
-      const int e = threadIdx.x + 256 * q;
-      const int ka = a_kfast ? (e & 15) : (e / TM), ia = a_kfast ? (e >> 4) : (e % TM);
-      const int kb = b_kfast ? (e & 15) : (e / TM), jb = b_kfast ? (e >> 4) : (e % TM);
-      As[buf][a_kfast ? ia * SK + ka : ka * PAD + ia] = pa[q];
-      Bs[buf][b_kfast ? jb * SK + kb : kb * PAD + jb] = pb[q];
+      *(gemm_f64x2_t*)&As[buf][(la + q * (256 / LPA)) * (AK ? SK : PAD) + pa2] = ra[q];
+      *(gemm_f64x2_t*)&Bs[buf][(lb + q * (256 / LPB)) * (BK ? SK : PAD) + pb2] = rb2[q];
     }
+  };
+  // fragments of quarter h of a k-tile
+  struct Frag {
+    double a[W], b[W];
+  };
+  auto frag = [&](Frag& f, int buf, int h) {
+    const int k = 4 * h + g;
+#pragma unroll
+    for (int rb = 0; rb < W; ++rb) {
+      const int i = TW * wm + 16 * rb + ln;
+      f.a[rb] = As[buf][AK ? i * SK + k : k * PAD + i];
+    }
+#pragma unroll
+    for (int cb = 0; cb < W; ++cb) {
+      const int j = TW * wn + 16 * cb + ln;
+      f.b[cb] = Bs[buf][BK ? j * SK + k : k * PAD + j];
+    }
+  };
+  auto mul = [&](const Frag& f) {
+#pragma unroll
+    for (int rb = 0; rb < W; ++rb)
+#pragma unroll
+      for (int cb = 0; cb < W; ++cb)
+        acc[rb][cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(f.a[rb], f.b[cb], acc[rb][cb], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
   };
   load(0);
   store(0);
   __syncthreads();
+  Frag f0, f1;
+  frag(f0, 0, 0);
   int buf = 0;
   for (int64_t k0 = 0; k0 < J.K; k0 += GK) {
     const bool more = k0 + GK < J.K;
     if (more) load(k0 + GK);
-#pragma unroll
-    for (int sub = 0; sub < GK / 4; ++sub) {
-      __builtin_amdgcn_sched_barrier(0);
-      double a[W], b[W];
-#pragma unroll
-      for (int rb = 0; rb < W; ++rb) {
-        const int i = TW * wm + 16 * rb + ln, k = 4 * sub + g;
-        a[rb] = As[buf][a_kfast ? i * SK + k : k * PAD + i];
-      }
-#pragma unroll
-      for (int cb = 0; cb < W; ++cb) {
-        const int j = TW * wn + 16 * cb + ln, k = 4 * sub + g;
-        b[cb] = Bs[buf][b_kfast ? j * SK + k : k * PAD + j];
-      }
-#pragma unroll
-      for (int rb = 0; rb < W; ++rb)
-#pragma unroll
-        for (int cb = 0; cb < W; ++cb)
-          acc[rb][cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[rb], b[cb], acc[rb][cb], 0, 0, 0);
-    }
+    frag(f1, buf, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    mul(f0);
+    frag(f0, buf, 2);
+    mul(f1);
+    frag(f1, buf, 3);
+    mul(f0);
     // the other buffer was last read before the previous step's barrier
-    if (more) store(buf ^ 1);
-    __syncthreads();
+    if (more) {
+      store(buf ^ 1);
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+      frag(f0, buf ^ 1, 0);
+    }
+    mul(f1);
     buf ^= 1;
   }
+  const bool mirror = J.upper == 2 && i0 != j0;
 #pragma unroll
   for (int rb = 0; rb < W; ++rb) {
     __builtin_amdgcn_sched_barrier(0);
@@ -1140,28 +1195,74 @@ __device__ __forceinline__ void gemm_tile_l(const GemmJob& J, int64_t i0, int64_
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int64_t gi = i0 + TW * wm + 16 * rb + g + 4 * v, gj = j0 + TW * wn + 16 * cb + ln;
-        if (gi < J.M && gj < J.N) {
+        if (FULL || (gi < J.M && gj < J.N)) {
           auto cp = gmem(J.C) + gi * J.cs0 + gj * J.cs1;
-          *cp = (J.beta == 0.0) ? J.alpha * acc[rb][cb][v] : J.alpha * acc[rb][cb][v] + J.beta * *cp;
+          const double x = (J.beta == 0.0) ? J.alpha * acc[rb][cb][v] : J.alpha * acc[rb][cb][v] + J.beta * *cp;
+          *cp = x;
+          if (mirror) gmem(J.C)[gj * J.cs0 + gi * J.cs1] = x;
         }
       }
   }
 }
 
+// Tile t of a job's gx x gy tiles (t < gx * gy, or the gx (gx + 1) / 2 on or above the diagonal):
+// columns of tiles in groups of four, so that the tiles that run together on an XCD (consecutive t)
+// share their operands' panels in its L2.
+__device__ __forceinline__ void gemm_tile_of(int t, int gx, int gy, bool upper, int& bx, int& by) {
+  int j0 = 0, wd = min(4, gy);
+  for (;;) {
+    const int rows = upper ? min(gx, j0 + wd) : gx;
+    if (t < rows * wd) break;
+    t -= rows * wd;
+    j0 += wd;
+    wd = min(4, gy - j0);
+  }
+  bx = t / wd;
+  by = j0 + t % wd;
+}
+
+// Tiles gemm_tile_of numbers (for `upper` a few of them lie below the diagonal).
+__host__ __device__ __forceinline__ int gemm_tiles(int gx, int gy, bool upper) {
+  if (!upper) return gx * gy;
+  int n = 0;
+  for (int j0 = 0; j0 < gy; j0 += 4) {
+    const int wd = (gy - j0 < 4) ? gy - j0 : 4;
+    n += ((gx < j0 + wd) ? gx : j0 + wd) * wd;
+  }
+  return n;
+}
+
 template <int W>
-__device__ __forceinline__ void gemm_tile(const GemmJob& J, int64_t bx, int64_t by) {
+__device__ __forceinline__ void gemm_tile(const GemmJob& J) {
   using T = GemmTile<W>;
-  __shared__ double As[2][T::BUF];
-  __shared__ double Bs[2][T::BUF];
-  const int64_t i0 = bx * T::TM, j0 = by * T::TM;
-  if (i0 >= J.M || j0 >= J.N || (J.upper && i0 > j0)) return;
+  __shared__ __attribute__((aligned(16))) double As[2][T::BUF];
+  __shared__ __attribute__((aligned(16))) double Bs[2][T::BUF];
+  if (J.M <= 0 || J.N <= 0) return;
+  // workgroups go to the eight XCDs in turn (gridDim.x is a multiple of 8): each takes a run of
+  // consecutive tiles
+  const int gx = (int)((J.M + T::TM - 1) / T::TM), gy = (int)((J.N + T::TM - 1) / T::TM);
+  const int nt = gemm_tiles(gx, gy, J.upper != 0), per = (nt + 7) / 8;
+  const int slot = blockIdx.x >> 3, t = (blockIdx.x & 7) * per + slot;
+  if (slot >= per || t >= nt) return;
   if (J.skip != nullptr && *J.skip != 0) return;
+  int bx, by;
+  gemm_tile_of(t, gx, gy, J.upper != 0, bx, by);
+  const int64_t i0 = (int64_t)bx * T::TM, j0 = (int64_t)by * T::TM;
+  if (J.upper && i0 > j0) return;
+  const int64_t far = max(max(J.as0, J.as1), max(J.bs0, J.bs1));   // a line's byte offset has to fit 32 bits
+  const bool full = i0 + T::TM <= J.M && j0 + T::TM <= J.N && far < (1ll << 31) / (8 * T::TM);
+  auto go = [&](auto ak, auto bk) {
+    if (full) gemm_tile_l<W, decltype(ak)::value, decltype(bk)::value, true>(J, i0, j0, As, Bs);
+    else gemm_tile_l<W, decltype(ak)::value, decltype(bk)::value, false>(J, i0, j0, As, Bs);
+  };
+  using Yes = std::integral_constant<bool, true>;
+  using No = std::integral_constant<bool, false>;
   if (J.as1 == 1) {
-    if (J.bs0 == 1) gemm_tile_l<W, true, true>(J, i0, j0, As, Bs);
-    else gemm_tile_l<W, true, false>(J, i0, j0, As, Bs);
+    if (J.bs0 == 1) go(Yes{}, Yes{});
+    else go(Yes{}, No{});
   } else {
-    if (J.bs0 == 1) gemm_tile_l<W, false, true>(J, i0, j0, As, Bs);
-    else gemm_tile_l<W, false, false>(J, i0, j0, As, Bs);
+    if (J.bs0 == 1) go(No{}, Yes{});
+    else go(No{}, No{});
   }
 }
 
@@ -1169,48 +1270,54 @@ __device__ __forceinline__ void gemm_tile(const GemmJob& J, int64_t bx, int64_t 
 template <int W>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_gemm_jobs(const GemmJob* __restrict__ jobs) {
   const GemmJob J = jobs[blockIdx.z];
-  gemm_tile<W>(J, blockIdx.x, blockIdx.y);
+  gemm_tile<W>(J);
 }
 
 // One job passed by value.
 template <int W>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_gemm_one(GemmJob J) {
-  gemm_tile<W>(J, blockIdx.x, blockIdx.y);
+  gemm_tile<W>(J);
 }
 
-// 128 x 128 tiles once the outputs are at least 256 on both sides, else 64 x 64.
-inline bool gemm_big(int64_t M, int64_t N) { return M >= 256 && N >= 256; }
+// Tile side for n products of M x N outputs: the largest of 128, 64 and 32 that still gives every
+// CU a workgroup and computes at most a quarter more padding than the next smaller one.  With fewer
+// workgroups than CUs the chip idles and one tile's serial k loop sets the time.
+inline int gemm_side(int64_t M, int64_t N, int64_t n) {
+  const int64_t cus = 256;
+  auto tiles = [&](int64_t side) { return ((M + side - 1) / side) * ((N + side - 1) / side); };
+  for (int side = 128; side > 32; side /= 2)
+    if (tiles(side) * n >= cus && 16 * tiles(side) <= 5 * tiles(side / 2)) return side;
+  return 32;
+}
 
-// njobs jobs from a device table, at most max_m x max_n outputs each.
-inline void gemm_jobs(const GemmJob* jobs, int njobs, int64_t max_m, int64_t max_n, hipStream_t s) {
-  if (gemm_big(max_m, max_n)) {
-    const dim3 g((unsigned)((max_m + 127) / 128), (unsigned)((max_n + 127) / 128), (unsigned)njobs);
-    k_gemm_jobs<4><<<g, 256, 0, s>>>(jobs);
-  } else {
-    const dim3 g((unsigned)((max_m + 63) / 64), (unsigned)((max_n + 63) / 64), (unsigned)njobs);
-    k_gemm_jobs<2><<<g, 256, 0, s>>>(jobs);
-  }
+inline unsigned gemm_grid(int64_t M, int64_t N, int side, bool upper) {
+  const int t = gemm_tiles((int)((M + side - 1) / side), (int)((N + side - 1) / side), upper);
+  return (unsigned)(8 * std::max(1, (t + 7) / 8));
+}
+
+// njobs jobs from a device table, at most max_m x max_n outputs each (upper: all of them `upper`).
+inline void gemm_jobs(const GemmJob* jobs, int njobs, int64_t max_m, int64_t max_n, hipStream_t s, bool upper = false) {
+  const int side = gemm_side(max_m, max_n, njobs);
+  const dim3 g(gemm_grid(max_m, max_n, side, upper), 1, (unsigned)njobs);
+  if (side == 128) k_gemm_jobs<4><<<g, 256, 0, s>>>(jobs);
+  else if (side == 64) k_gemm_jobs<2><<<g, 256, 0, s>>>(jobs);
+  else k_gemm_jobs<1><<<g, 256, 0, s>>>(jobs);
+}
+
+// One job with every field given (a sub-block product, the `upper` tiles).
+inline void gemm_job(const GemmJob& J, hipStream_t s) {
+  const int side = gemm_side(J.M, J.N, 1);
+  const unsigned g = gemm_grid(J.M, J.N, side, J.upper != 0);
+  if (side == 128) k_gemm_one<4><<<g, 256, 0, s>>>(J);
+  else if (side == 64) k_gemm_one<2><<<g, 256, 0, s>>>(J);
+  else k_gemm_one<1><<<g, 256, 0, s>>>(J);
 }
 
 // C(i,j) = alpha * sum_k A(i,k) B(k,j) + beta * C(i,j); X(i,k) at X[i*xs0 + k*xs1].
 inline void gemm(int64_t M, int64_t N, int64_t Kd, double alpha, const double* A, int64_t as0, int64_t as1,
                  const double* B, int64_t bs0, int64_t bs1, double beta, double* C, int64_t cs0, int64_t cs1,
                  hipStream_t s) {
-  const GemmJob J{A, B, C, as0, as1, bs0, bs1, cs0, cs1, M, N, Kd, alpha, beta, 0, nullptr};
-  if (gemm_big(M, N)) {
-    k_gemm_one<4><<<dim3((unsigned)((M + 127) / 128), (unsigned)((N + 127) / 128)), 256, 0, s>>>(J);
-  } else {
-    k_gemm_one<2><<<dim3((unsigned)((M + 63) / 64), (unsigned)((N + 63) / 64)), 256, 0, s>>>(J);
-  }
-}
-
-// One job with every field given (a sub-block product, the `upper` tiles).
-inline void gemm_job(const GemmJob& J, hipStream_t s) {
-  if (gemm_big(J.M, J.N)) {
-    k_gemm_one<4><<<dim3((unsigned)((J.M + 127) / 128), (unsigned)((J.N + 127) / 128)), 256, 0, s>>>(J);
-  } else {
-    k_gemm_one<2><<<dim3((unsigned)((J.M + 63) / 64), (unsigned)((J.N + 63) / 64)), 256, 0, s>>>(J);
-  }
+  gemm_job(GemmJob{A, B, C, as0, as1, bs0, bs1, cs0, cs1, M, N, Kd, alpha, beta, 0, nullptr}, s);
 }
 
 // ---- Cholesky factor of a symmetric positive definite matrix ------------------------------------
@@ -1332,7 +1439,7 @@ inline void cholesky_upper_jobs(const CholJob* jobs, int njobs, int64_t max_q, G
     if (rem <= 0) continue;
     k_chol_panel_jobs<<<dim3((unsigned)((rem + 255) / 256), (unsigned)njobs), 256, 0, s>>>(jobs, kb);
     k_chol_trail_jobs<<<1, 256, 0, s>>>(jobs, njobs, kb, trail);
-    gemm_jobs(trail, njobs, rem, rem, s);
+    gemm_jobs(trail, njobs, rem, rem, s, true);
   }
   k_chol_finish_jobs<<<dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>((max_q * max_q + 255) / 256, 4096)),
                             (unsigned)njobs), 256, 0, s>>>(jobs);

@@ -584,7 +584,7 @@ hipError_t polar_batch(const Tables& tb, int njobs, int64_t max_rows, int64_t ma
     for (int b = 0; b < kNsCheckSteps && step < kNsMaxSteps; ++b, ++step) {
       const int p = step & 1;
       k_ns_reset<<<1, 256, 0, s>>>(tb.nst, njobs);
-      gemm_jobs(tb.ngj[2 * p], njobs, max_q, max_q, s);
+      gemm_jobs(tb.ngj[2 * p], njobs, max_q, max_q, s, true);
       k_ns_stats<<<dim3(cb, (unsigned)njobs), 256, 0, s>>>(tb.ns, tb.nst);
       k_ns_form<<<dim3(fb, (unsigned)njobs), 256, 0, s>>>(tb.ns, tb.nst, scaled ? 1 : 0);
       gemm_jobs(tb.ngj[2 * p + 1], njobs, max_rows, max_q, s);
@@ -615,7 +615,7 @@ hipError_t polar_gram_batch(const Tables& tb, int njobs, int64_t max_q, std::vec
   const unsigned fb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((max_q * max_q + 255) / 256, 2048));
   k_ns_begin<<<1, 256, 0, s>>>(tb.ns, tb.nst, njobs, 1);
   k_ns_eye<<<dim3(fb, (unsigned)njobs), 256, 0, s>>>(tb.ns, tb.nst);
-  gemm_jobs(tb.qgj[0], njobs, max_q, max_q, s);
+  gemm_jobs(tb.qgj[0], njobs, max_q, max_q, s, true);
   hst.assign(njobs, NsState{});
   for (int step = 0; step < kNsMaxSteps;) {
     for (int b = 0; b < kNsCheckSteps && step < kNsMaxSteps; ++b, ++step) {
@@ -623,9 +623,9 @@ hipError_t polar_gram_batch(const Tables& tb, int njobs, int64_t max_q, std::vec
       k_ns_reset<<<1, 256, 0, s>>>(tb.nst, njobs);
       k_ns_stats<<<dim3(cb, (unsigned)njobs), 256, 0, s>>>(tb.ns, tb.nst);
       k_ns_form<<<dim3(fb, (unsigned)njobs), 256, 0, s>>>(tb.ns, tb.nst, 0);
-      gemm_jobs(tb.qgj[1], njobs, max_q, max_q, s);
-      gemm_jobs(tb.qgj[2], njobs, max_q, max_q, s);
-      gemm_jobs(tb.qgj[3 + p], njobs, max_q, max_q, s);
+      gemm_jobs(tb.qgj[1], njobs, max_q, max_q, s, true);
+      gemm_jobs(tb.qgj[2], njobs, max_q, max_q, s, true);
+      gemm_jobs(tb.qgj[3 + p], njobs, max_q, max_q, s, true);
       k_ns_step_end<<<1, 256, 0, s>>>(tb.nst, njobs);
     }
     hipError_t e = hipMemcpyAsync(hst.data(), tb.nst, sizeof(NsState) * njobs, hipMemcpyDeviceToHost, s);
@@ -708,21 +708,22 @@ iso_status run_batch(const iso_tensor* t, const std::vector<int>& ids, int K, is
       const int pj = 2 * e + h;
       const int64_t rows = h ? n : m;
       const int* skip = &tb.nst[pj].done;
-      // the tall side of a tall matrix iterates in q space
+      // the tall side of a tall matrix iterates in q space; its products are of polynomials in one
+      // Gram matrix, so they are symmetric and one triangle of tiles and its mirror form them
       const bool gs = pre[e] && rows > q;
       hn[pj] = gs ? NsJob{b.PG[h], q, b.QT, {b.QP[0], b.QP[1]}, 1} : NsJob{b.PG[h], q};
       if (gs) {
-        hq[0][pj] = GemmJob{b.PX[h][0], b.PX[h][0], b.PG[h], rows, 1, 1, rows, 1, q, q, q, rows, 1.0, 0.0, 0, skip};
-        hq[1][pj] = GemmJob{b.PG[h], b.QT, b.QH, 1, q, 1, q, 1, q, q, q, q, 1.0, 0.0, 0, skip};
-        hq[2][pj] = GemmJob{b.QT, b.QH, b.PG[h], 1, q, 1, q, 1, q, q, q, q, 1.0, 0.0, 0, skip};
-        hq[3][pj] = GemmJob{b.QP[0], b.QT, b.QP[1], 1, q, 1, q, 1, q, q, q, q, 1.0, 0.0, 0, skip};
-        hq[4][pj] = GemmJob{b.QP[1], b.QT, b.QP[0], 1, q, 1, q, 1, q, q, q, q, 1.0, 0.0, 0, skip};
+        hq[0][pj] = GemmJob{b.PX[h][0], b.PX[h][0], b.PG[h], rows, 1, 1, rows, 1, q, q, q, rows, 1.0, 0.0, 2, skip};
+        hq[1][pj] = GemmJob{b.PG[h], b.QT, b.QH, 1, q, 1, q, 1, q, q, q, q, 1.0, 0.0, 2, skip};
+        hq[2][pj] = GemmJob{b.QT, b.QH, b.PG[h], 1, q, 1, q, 1, q, q, q, q, 1.0, 0.0, 2, skip};
+        hq[3][pj] = GemmJob{b.QP[0], b.QT, b.QP[1], 1, q, 1, q, 1, q, q, q, q, 1.0, 0.0, 2, skip};
+        hq[4][pj] = GemmJob{b.QP[1], b.QT, b.QP[0], 1, q, 1, q, 1, q, q, q, q, 1.0, 0.0, 2, skip};
       }
       for (int p = 0; p < 2; ++p) {
         const double* X = b.PX[h][p];
         double* Y = b.PX[h][1 - p];
-        // G = X^T X (q x q), X (rows x q) col-major
-        hg[2 * p][pj] = GemmJob{X, X, b.PG[h], rows, 1, 1, rows, 1, q, q, q, rows, 1.0, 0.0, 0, skip};
+        // G = X^T X (q x q), X (rows x q) col-major, one triangle of tiles and its mirror
+        hg[2 * p][pj] = GemmJob{X, X, b.PG[h], rows, 1, 1, rows, 1, q, q, q, rows, 1.0, 0.0, 2, skip};
         // Y = X T (rows x q)
         hg[2 * p + 1][pj] = GemmJob{X, b.PG[h], Y, 1, rows, 1, q, 1, rows, rows, q, q, 1.0, 0.0, 0, skip};
       }
@@ -1161,7 +1162,7 @@ iso_status run_optimizer(const iso_frame* f, int n_f, iso_dtype dt, const iso_ad
       for (int p = 0; p < 2; ++p) {
         const double* X = b.PX[h][p];
         double* Y = b.PX[h][1 - p];
-        hg[2 * p][pj] = GemmJob{X, X, b.PG[h], rows, 1, 1, rows, 1, q, q, q, rows, 1.0, 0.0, 0, skip};
+        hg[2 * p][pj] = GemmJob{X, X, b.PG[h], rows, 1, 1, rows, 1, q, q, q, rows, 1.0, 0.0, 2, skip};
         hg[2 * p + 1][pj] = GemmJob{X, b.PG[h], Y, 1, rows, 1, q, 1, rows, rows, q, q, 1.0, 0.0, 0, skip};
       }
     }

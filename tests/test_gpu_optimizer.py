@@ -179,3 +179,38 @@ def test_muon_zero_and_ill_conditioned_directions():
             ref_w = w_ref.ravel()
             scale = np.maximum(np.abs(ref_w), 2.0 ** -10 * np.abs(ref_w).max())
             assert np.max(np.abs(w.astype(np.float64) - ref_w) / scale) <= 1e-6, (kind, t)
+
+
+@pytest.mark.parametrize("shapes", [
+    [(1, 1, 1), (31, 33, 31), (65, 32, 17), (15, 130, 15)],      # 32-wide product tiles, k shorter than one step
+    [(1025, 1030, 1023)],                                        # 64-wide tiles, one row past, one column short
+    [(513, 516, 513)] * 8,                                       # 128-wide tiles in the batched products
+], ids=["tile32", "tile64", "tile128"])
+def test_product_tile_edges(shapes):
+    """One ISO-AdamW step at the edges of the product tiles (each tile side is chosen by how many tiles the
+    outputs make): gradients, both polar factors' Gram (one triangle and its mirror) and step products, W+.
+    Bars of the three-step test."""
+    import torch
+    rng = np.random.default_rng(41)
+    frames, want = [], []
+    hp = dict(lr=0.02, beta1=0.9, beta2=0.999, eps=1e-8, weight_decay=0.01)
+    for m, n, q in shapes:
+        u, _ = np.linalg.qr(rng.standard_normal((m, q)))
+        v, _ = np.linalg.qr(rng.standard_normal((n, q)))
+        s = np.sort(rng.uniform(0.5, 2.0, q))[::-1].copy()
+        g_store = nm.from_f64(rng.standard_normal(m * n) * 0.1, "f32")
+        g = nm.to_f64(g_store, "f32").reshape(m, n)
+        z = (np.zeros((m, q)), np.zeros((m, q)), np.zeros((n, q)), np.zeros((n, q)))
+        frames.append(iso.Frame(rows=m, cols=n, rank=q, u=_colmajor(u), v=_colmajor(v), sigma=torch.tensor(s, device="cuda"),
+                                m_u=_colmajor(z[0]), v_u=_colmajor(z[1]), m_v=_colmajor(z[2]), v_v=_colmajor(z[3]),
+                                grad=to_dev(g_store), w_out=torch.empty(m * n, dtype=torch.int32, device="cuda")))
+        want.append(op.iso_adamw_step(u, v, s, g, z, 1, hp["lr"], hp["beta1"], hp["beta2"], hp["eps"], hp["weight_decay"]))
+    ws = iso.optimizer_workspace(frames)
+    say(f"iso-adamw tile edges: {shapes}")
+    iso.iso_optimizer_step(frames, iso.F32, step=1, ws=ws, **hp)
+    assert iso.iso_read_device_status(ws) == 0
+    for F, (u, v, w, _) in zip(frames, want):
+        assert np.abs(_back(F.u, F.rows, F.rank) - u).max() <= 1e-10
+        assert np.abs(_back(F.v, F.cols, F.rank) - v).max() <= 1e-10
+        got, ref = from_dev(F.w_out, F.rows * F.cols, "f32").astype(np.float64), w.ravel()
+        assert np.max(np.abs(got - ref) / np.maximum(np.abs(ref), 2.0 ** -10 * np.abs(ref).max())) <= 1e-6
