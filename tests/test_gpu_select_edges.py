@@ -1,0 +1,44 @@
+"""TopKMask at the edges of its kernels' work units, against the oracle, exactly: mask words (32 entries, eight per
+lane, 8192 per workgroup step), tensors that fill their last vector, word or chunk by one entry or miss it by one.
+"""
+import numpy as np
+import pytest
+
+from oracle import numerics as nm
+from oracle import ties
+
+from tests.gpu_helpers import Unit, bits_to_mask, run_topk, say
+
+pytestmark = pytest.mark.gpu
+
+
+def _unit(rng, n, k, dtype, K=2):
+    # coarse values: many entries share the threshold magnitude, so the flat-index rule decides
+    ds = []
+    for _ in range(K):
+        v = np.round(rng.standard_normal(n) * 6.0) / 4096.0
+        v[rng.random(n) < 0.3] = 0.0
+        ds.append(nm.from_f64(v, dtype))
+    return Unit(1, n, nm.from_f64(np.zeros(n), dtype), ds, dtype, k)
+
+
+def check(units, K, dtype):
+    d, bits, st, _ = run_topk(units, K, dtype, with_bits=True)
+    assert st == 0
+    for j, u in enumerate(units):
+        for i in range(K):
+            got, want = d[j * K + i], ties.topk_descriptor(u.deltas[i], u.k, dtype)
+            assert (got[0], got[2], got[3], got[4]) == want, (u.n, u.k, i, got, want)
+            assert got[1] == int(nm.magnitude_key(u.deltas[i], dtype).max())
+            assert np.array_equal(bits_to_mask(bits[j * K + i], u.n), ties.topk_mask(u.deltas[i], u.k, dtype)), (u.n, u.k)
+            tail = int(bits[j * K + i][-1]) >> (u.n % 32 or 32)
+            assert tail == 0, "bits past the end are zero"
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_mask_word_edges(dtype):
+    rng = np.random.default_rng(71)
+    units = [_unit(rng, n, k, dtype) for n in (1, 7, 8, 9, 31, 32, 33, 255, 257, 8191, 8192, 8193, 24577)
+             for k in {0, 1, n // 3, n}]
+    say(f"mask word edges {dtype}")
+    check(units, 2, dtype)
