@@ -151,8 +151,6 @@ Layout plan(int op, const iso_tensor* t, int n_t, int K, int dt) {
   off = align_up(off + sizeof(int64_t) * (size_t)n_t, 256);
   L.ptrs = off;
   off = align_up(off + sizeof(void*) * (size_t)n_t * K, 256);
-  int64_t sumnk = 0;
-  for (int j = 0; j < n_t; ++j) sumnk += t[j].rows * t[j].cols * (int64_t)K;
   const int64_t te = merge_tile_elems(dt);
   for (int j = 0; j < n_t; ++j) L.tiles += (t[j].rows * t[j].cols + te - 1) / te;
   L.tmap = off;
@@ -173,8 +171,9 @@ Layout plan(int op, const iso_tensor* t, int n_t, int K, int dt) {
     }
   }
   L.upload_end = off;
+  L.fused = fused_eligible(op, n_t, dt) && L.n_groups == 0;
   if (L.select) {
-    L.hist_chunk = hist_chunk_for(sumnk);
+    L.hist_chunk = hist_chunk_for(t, n_t, K, dt, L.fused);
     for (int j = 0; j < n_t; ++j) {
       const int64_t n = t[j].rows * t[j].cols;
       L.hist_items += K * ((n + L.hist_chunk - 1) / L.hist_chunk);
@@ -204,7 +203,6 @@ Layout plan(int op, const iso_tensor* t, int n_t, int K, int dt) {
       off = align_up(off + sizeof(int64_t) * 2 * (size_t)n_t * K, 256);
     }
   }
-  L.fused = fused_eligible(op, n_t, dt) && L.n_groups == 0;
   if (L.fused) {
     for (int j = 0; j < n_t; ++j) L.ritems += fused_reduce_items(t[j].rows * t[j].cols, K);
     for (int j = 0; j < n_t; ++j) L.groups += fused_groups(t[j].rows * t[j].cols);

@@ -46,7 +46,8 @@ struct SelectPlan {
   int64_t* mcnt = nullptr;          // 2 * n_t * K: per unit, entries above the group threshold and ties
 };
 
-int64_t hist_chunk_for(int64_t total_elems_times_k);
+// chunk of the histogram passes; fallback: the passes only serve tensors the single-read path gives up
+int64_t hist_chunk_for(const iso_tensor* t, int n_t, int K, int dt, bool fallback);
 hipError_t fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t s);
 hipError_t run_select(const SelectPlan& pl, int dt, hipStream_t s);
 int select_last_bits(int dt);

@@ -98,12 +98,34 @@ __device__ __forceinline__ void item_of(const int64_t* item0, int n_t, int K, in
 // ---- histogram pass -----------------------------------------------------------------------------
 // With `dump` set (last pass only), the block also stores its chunk histogram (bin 0 =
 // in-bucket entries whose digit is 0) so ties can later be located without another read.
+//
+// One workgroup per CU (128 KB of bins), so nothing overlaps its phases: clearing, counting (the
+// chunk at the CU's share of HBM, LDS atomics and the key arithmetic), and the flush of the
+// nonzero bins.  The bf16 pass does only what its keys need: digit 0 (a zero) is not counted but
+// follows from the chunk's size, and the largest key is the highest bin in use.  Bins are cleared and
+// flushed 16 bytes at a time.
 
 struct HistLds {
   uint32_t bins[kMaxBins];
   uint32_t wmax[16];
-  uint32_t wzero[16];
+  uint32_t wsum[16];
 };
+
+// Block sum and maximum (1024 threads) of one value each, in every thread.
+__device__ __forceinline__ void hist_reduce(uint32_t& sum, uint32_t& mx, HistLds& sm) {
+  for (int o = 32; o > 0; o >>= 1) sum += (uint32_t)__shfl_xor((int)sum, o, 64);
+  mx = wave_max_u32(mx);
+  if ((threadIdx.x & 63) == 0) {
+    sm.wsum[threadIdx.x >> 6] = sum;
+    sm.wmax[threadIdx.x >> 6] = mx;
+  }
+  __syncthreads();
+  sum = mx = 0;
+  for (int w = 0; w < (int)(blockDim.x >> 6); ++w) {
+    sum += sm.wsum[w];
+    mx = max(mx, sm.wmax[w]);
+  }
+}
 
 // One histogram work item: chunk c of delta i of tensor j; `item` numbers its dump slot.
 template <int DT>
@@ -111,16 +133,15 @@ __device__ void hist_item(const DevTensor* __restrict__ tab, int K, int j, int i
                           int64_t chunk, UnitState* __restrict__ st, uint32_t* __restrict__ hist, int shift,
                           int bits, int first, uint32_t* status, uint32_t* __restrict__ dump, HistLds& sm) {
   using F = Fmt<DT>;
+  constexpr bool kBf = DT == ISO_BF16;         // one pass over the whole key
   constexpr int U = 8;                         // 16-byte loads in flight per thread
   uint32_t* lds = sm.bins;
-  uint32_t* wmax = sm.wmax;
-  uint32_t* wzero = sm.wzero;
   const int u = j * K + i;
   const DevTensor& T = tab[j];
   const bool active = !st[u].done;             // k == 0 units only need key_max from the first pass
   if (!first && !active) return;               // uniform per block
   const uint32_t nb = 1u << bits;
-  for (uint32_t b = threadIdx.x; b < nb; b += blockDim.x) lds[b] = 0;
+  for (uint32_t v = threadIdx.x; v < nb / 4; v += blockDim.x) ((uint4*)lds)[v] = make_uint4(0, 0, 0, 0);
   __syncthreads();
 
   const int hs = shift + bits;                 // bits above the digit must match the prefix
@@ -132,11 +153,15 @@ __device__ void hist_item(const DevTensor* __restrict__ tab, int K, int j, int i
   uint32_t kmax = 0, nzero = 0;
 
   auto count = [&](uint32_t key) {
-    if (first) kmax = max(kmax, key);
-    bool match = active && (first || ((key >> hs) == want));
-    uint32_t d = (key >> shift) & dmask;
-    if (match && d != 0u) atomicAdd(&lds[d], 1u);
-    nzero += (match && d == 0u);
+    if constexpr (kBf) {
+      if (key != 0u) atomicAdd(&lds[key], 1u);
+    } else {
+      if (first) kmax = max(kmax, key);
+      bool match = active && (first || ((key >> hs) == want));
+      uint32_t d = (key >> shift) & dmask;
+      if (match && d != 0u) atomicAdd(&lds[d], 1u);
+      nzero += (match && d == 0u);
+    }
   };
 
   const int64_t v0 = e0 / F::kPerVec;
@@ -152,11 +177,11 @@ __device__ void hist_item(const DevTensor* __restrict__ tab, int K, int j, int i
 #pragma unroll
     for (int q = 0; q < U; ++q) {
       int64_t vv = v + (int64_t)q * blockDim.x;
-      if (vv >= v1) break;
+      if (!kBf && vv >= v1) break;             // bf16: the zero fill counts nothing
       uint32_t w[4] = {a[q].x, a[q].y, a[q].z, a[q].w};
 #pragma unroll
       for (int h = 0; h < 4; ++h) {
-        if constexpr (DT == ISO_BF16) {
+        if constexpr (kBf) {
           count(w[h] & 0x7FFFu);
           count((w[h] >> 16) & 0x7FFFu);
         } else {
@@ -168,36 +193,40 @@ __device__ void hist_item(const DevTensor* __restrict__ tab, int K, int j, int i
   // scalar tail (last chunk of a tensor whose size is not a multiple of the vector width)
   for (int64_t e = v1 * F::kPerVec + threadIdx.x; e < e1; e += blockDim.x)
     count(elem_bits<DT>(p, e) & F::kKeyMask);
-  uint32_t zsum = 0;
-  if (dump != nullptr) {
-    uint32_t z = nzero;
-    for (int o = 32; o > 0; o >>= 1) z += (uint32_t)__shfl_xor((int)z, o, 64);
-    if ((threadIdx.x & 63) == 0) wzero[threadIdx.x >> 6] = z;
-  }
   __syncthreads();
-  if (dump != nullptr) {
-    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) zsum += wzero[w];
-  }
 
-  uint32_t* gh = hist + (size_t)u * kMaxBins;
-  if (active) {
-    uint32_t* dp = (dump != nullptr) ? dump + (size_t)item * nb : nullptr;
-    for (uint32_t b = threadIdx.x; b < nb; b += blockDim.x) {
-      uint32_t cnt = lds[b];
-      if (cnt) atomicAdd(&gh[b], cnt);
-      if (dp) dp[b] = (b == 0) ? zsum : cnt;
+  uint4* gh = (uint4*)(hist + (size_t)u * kMaxBins);
+  uint4* dp = (active && dump != nullptr) ? (uint4*)(dump + (size_t)item * nb) : nullptr;
+  uint32_t nz = 0;                             // bf16: entries counted in this thread's bins
+  if (active || kBf) {
+    for (uint32_t v = threadIdx.x; v < nb / 4; v += blockDim.x) {
+      const uint4 x = ((const uint4*)lds)[v];
+      if (active) {
+        if (x.x) atomicAdd(&gh[v].x, x.x);
+        if (x.y) atomicAdd(&gh[v].y, x.y);
+        if (x.z) atomicAdd(&gh[v].z, x.z);
+        if (x.w) atomicAdd(&gh[v].w, x.w);
+        if (dp != nullptr && v != 0) dp[v] = x;
+      }
+      if constexpr (kBf) {
+        nz += x.x + x.y + x.z + x.w;
+        const uint32_t top = x.w ? 3u : x.z ? 2u : x.y ? 1u : 0u;
+        if (x.x | x.y | x.z | x.w) kmax = 4 * v + top;
+      }
     }
   }
-  if (first) {
-    uint32_t m = wave_max_u32(kmax);
-    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      uint32_t mm = 0;
-      for (int w = 0; w < (int)(blockDim.x >> 6); ++w) mm = max(mm, wmax[w]);
-      atomicMax(&st[u].key_max, mm);
-      uint32_t expfield = (DT == ISO_BF16) ? 0x7F80u : 0x7F800000u;
-      if (mm >= expfield) flag_status(status, kStatusNonFinite);
+  uint32_t sum = kBf ? nz : nzero;
+  if (kBf || first || dp != nullptr) hist_reduce(sum, kmax, sm);
+  if (threadIdx.x == 0) {
+    if (dp != nullptr) {
+      uint4 x = ((const uint4*)lds)[0];
+      x.x = kBf ? (uint32_t)(e1 - e0) - sum : sum;
+      dp[0] = x;
+    }
+    if (first) {
+      atomicMax(&st[u].key_max, kmax);
+      const uint32_t expfield = kBf ? 0x7F80u : 0x7F800000u;
+      if (kmax >= expfield) flag_status(status, kStatusNonFinite);
     }
   }
   __syncthreads();                             // LDS is reused by the block's next item
@@ -209,7 +238,7 @@ __global__ void __launch_bounds__(kHistThreads) k_hist(const DevTensor* __restri
                                                        UnitState* __restrict__ st, uint32_t* __restrict__ hist,
                                                        int shift, int bits, int first, uint32_t* status,
                                                        uint32_t* __restrict__ dump) {
-  __shared__ HistLds sm;
+  __shared__ __attribute__((aligned(16))) HistLds sm;
   int j, i;
   int64_t c;
   item_of(item0, n_t, K, chunk, tab, blockIdx.x, j, i, c);
@@ -225,7 +254,7 @@ __global__ void __launch_bounds__(kHistThreads) k_hist_flagged(const DevTensor* 
                                                                int first, uint32_t* status,
                                                                uint32_t* __restrict__ dump,
                                                                const int* __restrict__ filter) {
-  __shared__ HistLds sm;
+  __shared__ __attribute__((aligned(16))) HistLds sm;
   __shared__ int sflag[1024];
   for_flagged_items(
       filter, n_t, sflag, [&](int j) { return (int64_t)K * ((tab[j].n + chunk - 1) / chunk); },
@@ -769,10 +798,33 @@ __global__ void k_fill_u32(uint32_t* p, int64_t n, uint32_t v) {
 
 // ---- host-side launch sequence ------------------------------------------------------------------
 
-int64_t hist_chunk_for(int64_t total_elems_times_k) {
-  int64_t c = 1 << 16;
-  while (c < (1 << 20) && total_elems_times_k / c > 2048) c <<= 1;
-  return c;
+// Entries per histogram work item.  At most 2048 items, in chunks of 2^16 to 2^20 entries, is the
+// coarse rule (and the only one where the histogram is the single-read path's fallback).  A CU runs
+// one item at a time, and an item costs about as much as 2^16 bf16 (2^15 fp32) entries besides its
+// entries (clearing, flush and dump of its bins), so among the larger chunks the one with the least
+// waves * (entries + overhead) is taken.  12 deltas of 4.2M to 8.4M bf16 entries: 1028 items of 2^16
+// in five waves -> 252 items in one, the select and what follows it 268 -> 235 us.
+int64_t hist_chunk_for(const iso_tensor* t, int n_t, int K, int dt, bool fallback) {
+  int64_t total = 0;
+  for (int j = 0; j < n_t; ++j) total += t[j].rows * t[j].cols * (int64_t)K;
+  const int64_t most = 1 << 20;
+  int64_t c0 = 1 << 16;
+  while (c0 < most && total / c0 > 2048) c0 <<= 1;
+  if (fallback || c0 == most) return c0;
+  const int64_t overhead = (dt == ISO_BF16) ? 1 << 16 : 1 << 15;
+  int64_t best = c0, best_cost = INT64_MAX;
+  for (int64_t oct = c0; oct <= most; oct *= 2)
+    for (int64_t c = oct; c < 2 * oct && c <= most; c += oct / 8) {
+      int64_t items = 0;
+      for (int j = 0; j < n_t; ++j) items += K * ((t[j].rows * t[j].cols + c - 1) / c);
+      const int64_t cost = (items + 255) / 256 * (c + overhead);
+      if (cost < best_cost) {
+        best = c;
+        best_cost = cost;
+      }
+      if (items <= 256) return best;             // a larger chunk only lengthens the one wave
+    }
+  return best;
 }
 
 hipError_t fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t s) {
