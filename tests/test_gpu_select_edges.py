@@ -42,3 +42,19 @@ def test_mask_word_edges(dtype):
              for k in {0, 1, n // 3, n}]
     say(f"mask word edges {dtype}")
     check(units, 2, dtype)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_tie_cutoff_inside_chunks(dtype):
+    """The quota-th threshold entry in the first, the last and a middle segment of a chunk, in a chunk that ends
+    inside a vector, and beside a tensor of several chunks."""
+    rng = np.random.default_rng(72)
+    units = []
+    for n in (511, 512, 513, 1025, 66049, 140001, 262144):
+        v = np.where(rng.random(n) < 0.5, 1.0, 2.0) * np.where(rng.random(n) < 0.5, 1.0, -1.0)
+        big = int((np.abs(v) == 2.0).sum())
+        for k in {big + 1, big + (n - big) // 2, n - 1}:
+            units.append(Unit(1, n, nm.from_f64(np.zeros(n), dtype), [nm.from_f64(v, dtype), nm.from_f64(-v[::-1], dtype)],
+                              dtype, k))
+    say(f"tie cutoff {dtype}")
+    check(units, 2, dtype)
