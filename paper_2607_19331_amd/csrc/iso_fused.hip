@@ -81,9 +81,13 @@ __device__ int64_t block_scan(int64_t v, int64_t* sh /* >= 17 */) {
 
 // ---- 0. per-call state -------------------------------------------------------------------------
 
+// hist: the units' sample histograms, cleared when the sample is split (else null).
 __global__ void k_fs_init(const DevTensor* __restrict__ tab, int n_t, int K, FusedUnit* __restrict__ fu,
-                          int* __restrict__ tflag) {
+                          int* __restrict__ tflag, uint32_t* __restrict__ hist) {
   const int u = blockIdx.x * blockDim.x + threadIdx.x;
+  if (hist != nullptr)
+    for (int64_t v = u; v < (int64_t)n_t * K * (kBins / 4); v += (int64_t)gridDim.x * blockDim.x)
+      ((uint4*)hist)[v] = make_uint4(0, 0, 0, 0);
   if (u < n_t) tflag[u] = 0;
   if (u >= n_t * K) return;
   const DevTensor& T = tab[u / K];
@@ -101,23 +105,16 @@ __global__ void k_fs_init(const DevTensor* __restrict__ tab, int n_t, int K, Fus
   fu[u] = f;
 }
 
-// ---- 1. sample and bracket (one workgroup per delta) -------------------------------------------
+// ---- 1. sample and bracket ---------------------------------------------------------------------
 
-__global__ void __launch_bounds__(1024) k_fs_sample(const DevTensor* __restrict__ tab, int K,
-                                                    FusedUnit* __restrict__ fu, int* __restrict__ tflag) {
-  __shared__ uint32_t bins[kBins];
-  __shared__ int64_t sh[17];
-  __shared__ int32_t found[3];
-  const int u = blockIdx.x;
-  const int j = u / K, i = u % K;
-  const DevTensor& T = tab[j];
-  if (fu[u].flags & (kFusedNone | kFusedAll)) return;
-  for (int b = threadIdx.x; b < kBins; b += blockDim.x) bins[b] = 0;
-  if (threadIdx.x < 3) found[threadIdx.x] = -1;
+// Part `part` of `parts` of a delta's sample into the block's LDS histogram (cleared here); returns
+// the entries of the whole sample.  Two costs per part: the clearing of 128 KB of bins, then loads and LDS
+// atomics at one CU's rate (a whole sample of 2^20 entries takes one workgroup 70 us).
+__device__ __forceinline__ int64_t sample_part(const DevTensor& T, int i, int part, int parts, uint32_t* bins) {
+  for (int b = threadIdx.x; b < kBins / 4; b += blockDim.x) ((uint4*)bins)[b] = make_uint4(0, 0, 0, 0);
   __syncthreads();
   const int64_t n = T.n;
   const uint4* pv = (const uint4*)T.deltas[i];
-  const bool exact = n <= kExactMax;
   auto count8 = [&](const uint4& a) {
     const uint32_t w[4] = {a.x, a.y, a.z, a.w};
 #pragma unroll
@@ -130,59 +127,65 @@ __global__ void __launch_bounds__(1024) k_fs_sample(const DevTensor* __restrict_
   // kInFlight 16-byte loads per thread before any is counted: one workgroup per CU (the
   // histogram takes 128 KB of LDS), so the loads in flight set the rate
   constexpr int kInFlight = 16;
-  int64_t ns;
-  if (exact) {
-    const int64_t nvec = n / 8;
-    for (int64_t v = threadIdx.x; v < nvec; v += kInFlight * (int64_t)blockDim.x) {
+  if (n <= kExactMax) {
+    const int64_t nvec = n / 8, v1 = nvec * (part + 1) / parts;
+    for (int64_t v = nvec * part / parts + threadIdx.x; v < v1; v += kInFlight * (int64_t)blockDim.x) {
       uint4 a[kInFlight];
 #pragma unroll
       for (int q = 0; q < kInFlight; ++q) {
         const int64_t vv = v + q * (int64_t)blockDim.x;
-        a[q] = (vv < nvec) ? ld_stream(pv + vv) : make_uint4(0, 0, 0, 0);
+        a[q] = (vv < v1) ? ld_stream(pv + vv) : make_uint4(0, 0, 0, 0);
       }
 #pragma unroll
       for (int q = 0; q < kInFlight; ++q) count8(a[q]);   // the zero fill adds nothing
     }
-    const uint16_t* p = (const uint16_t*)T.deltas[i];
-    for (int64_t e = nvec * 8 + threadIdx.x; e < n; e += blockDim.x) {
-      const uint32_t k = bkey(p[e]);
-      if (k) atomicAdd(&bins[k], 1u);
-    }
-    ns = n;
-  } else {
-    // block b starts at entry floor(b * nb / kSampleBlocks) * kSampleSpan, nb = n / kSampleSpan
-    // (n > kExactMax, so the blocks are distinct); 32 threads, one 16-byte vector each, per block
-    const int64_t nb = n / kSampleSpan;
-    constexpr int kVecPerBlock = kSampleSpan / 8;
-    const int per_iter = blockDim.x / kVecPerBlock;
-    const int lb = threadIdx.x / kVecPerBlock, lv = threadIdx.x % kVecPerBlock;
-    for (int b0 = 0; b0 < kSampleBlocks; b0 += kInFlight * per_iter) {
-      uint4 a[kInFlight];
-#pragma unroll
-      for (int q = 0; q < kInFlight; ++q) {
-        const int b = b0 + q * per_iter + lb;
-        if (b < kSampleBlocks) {
-          const int64_t blk = (int64_t)b * nb / kSampleBlocks;
-          a[q] = ld_stream(pv + blk * kVecPerBlock + lv);
-        } else {
-          a[q] = make_uint4(0, 0, 0, 0);
-        }
+    if (part == parts - 1) {
+      const uint16_t* p = (const uint16_t*)T.deltas[i];
+      for (int64_t e = nvec * 8 + threadIdx.x; e < n; e += blockDim.x) {
+        const uint32_t k = bkey(p[e]);
+        if (k) atomicAdd(&bins[k], 1u);
       }
-#pragma unroll
-      for (int q = 0; q < kInFlight; ++q) count8(a[q]);
     }
-    ns = (int64_t)kSampleBlocks * kSampleSpan;
+    return n;
   }
+  // block b starts at entry floor(b * nb / kSampleBlocks) * kSampleSpan, nb = n / kSampleSpan
+  // (n > kExactMax, so the blocks are distinct); 32 threads, one 16-byte vector each, per block
+  const int64_t nb = n / kSampleSpan;
+  constexpr int kVecPerBlock = kSampleSpan / 8;
+  const int per_iter = blockDim.x / kVecPerBlock;
+  const int lb = threadIdx.x / kVecPerBlock, lv = threadIdx.x % kVecPerBlock;
+  const int b1 = kSampleBlocks * (part + 1) / parts;
+  for (int b0 = kSampleBlocks * part / parts; b0 < b1; b0 += kInFlight * per_iter) {
+    uint4 a[kInFlight];
+#pragma unroll
+    for (int q = 0; q < kInFlight; ++q) {
+      const int b = b0 + q * per_iter + lb;
+      if (b < b1) {
+        const int64_t blk = (int64_t)b * nb / kSampleBlocks;
+        a[q] = ld_stream(pv + blk * kVecPerBlock + lv);
+      } else {
+        a[q] = make_uint4(0, 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kInFlight; ++q) count8(a[q]);
+  }
+  return (int64_t)kSampleBlocks * kSampleSpan;
+}
+
+// Bracket of unit u from the sample's histogram in LDS (ns entries sampled of n; exact: all of them).
+__device__ void bracket_from(FusedUnit& F, int* tflag, const uint32_t* bins, int64_t ns, int64_t n, bool exact,
+                             int64_t* sh, int32_t* found) {
+  if (threadIdx.x < 3) found[threadIdx.x] = -1;
   __syncthreads();
   // thread t owns bins [32t, 32t + 32); sample keys above its range = total - inclusive prefix
   constexpr int kPer = kBins / 1024;
   int64_t mine = 0;
-  if (threadIdx.x < kBins / kPer)
-    for (int q = 0; q < kPer; ++q) mine += bins[threadIdx.x * kPer + q];
+  for (int q = 0; q < kPer; ++q) mine += bins[threadIdx.x * kPer + (q + threadIdx.x) % kPer];   // conflict-free order
   const int64_t incl = block_scan(mine, sh);
   const int64_t total = sh[16];
   // sample ranks (1-based, from the largest key) of the bracket ends and of the estimate
-  const int64_t k = fu[u].k;
+  const int64_t k = F.k;
   int64_t want[3];
   bool top_open = false;
   if (exact) {
@@ -198,8 +201,10 @@ __global__ void __launch_bounds__(1024) k_fs_sample(const DevTensor* __restrict_
     want[1] = (int64_t)fmin(r_lo, (double)ns);
     want[2] = max<int64_t>(1, (int64_t)llround(rhat));
   }
-  if (threadIdx.x < kBins / kPer) {
-    int64_t run = total - incl;
+  const int64_t above = total - incl;
+  if ((above < want[0] && above + mine >= want[0]) || (above < want[1] && above + mine >= want[1]) ||
+      (above < want[2] && above + mine >= want[2])) {
+    int64_t run = above;
     for (int q = kPer - 1; q >= 0; --q) {
       const int code = threadIdx.x * kPer + q;
       const int64_t c = bins[code];
@@ -215,13 +220,68 @@ __global__ void __launch_bounds__(1024) k_fs_sample(const DevTensor* __restrict_
     const uint32_t hi = top_open ? 0x7FFFu : (uint32_t)max(found[0], 0);
     const uint32_t lo = (uint32_t)max(found[1], 0);
     const uint32_t est = (uint32_t)max(found[2], 0);
-    FusedUnit& F = fu[u];
     F.lo = lo;
     F.hi = max(hi, lo);
     F.prov = max(lo, min(F.hi, est));
-    if (F.hi - lo + 1u > (uint32_t)kFusedMaxW) atomicOr(&tflag[j], kFlagWide);
+    if (F.hi - lo + 1u > (uint32_t)kFusedMaxW) atomicOr(tflag, kFlagWide);
   }
 }
+
+// One workgroup per delta: calls with enough deltas to fill the chip.
+__global__ void __launch_bounds__(1024) k_fs_sample(const DevTensor* __restrict__ tab, int K,
+                                                    FusedUnit* __restrict__ fu, int* __restrict__ tflag) {
+  __shared__ __attribute__((aligned(16))) uint32_t bins[kBins];
+  __shared__ int64_t sh[17];
+  __shared__ int32_t found[3];
+  const int u = blockIdx.x;
+  const DevTensor& T = tab[u / K];
+  if (fu[u].flags & (kFusedNone | kFusedAll)) return;
+  const int64_t ns = sample_part(T, u % K, 0, 1, bins);
+  __syncthreads();
+  bracket_from(fu[u], &tflag[u / K], bins, ns, T.n, T.n <= kExactMax, sh, found);
+}
+
+// Fewer deltas than CUs: each delta's sample split over gridDim.x workgroups that add their nonzero
+// bins to the delta's global histogram, then one workgroup per delta for the bracket.
+__global__ void __launch_bounds__(1024) k_fs_sample_part(const DevTensor* __restrict__ tab, int K,
+                                                         const FusedUnit* __restrict__ fu, uint32_t* __restrict__ hist) {
+  __shared__ __attribute__((aligned(16))) uint32_t bins[kBins];
+  const int u = blockIdx.y;
+  if (fu[u].flags & (kFusedNone | kFusedAll)) return;
+  sample_part(tab[u / K], u % K, blockIdx.x, gridDim.x, bins);
+  __syncthreads();
+  uint32_t* gh = hist + (size_t)u * kBins;
+  for (int v = threadIdx.x; v < kBins / 4; v += blockDim.x) {
+    const uint4 x = ((const uint4*)bins)[v];
+    if (x.x) atomicAdd(&gh[4 * v], x.x);
+    if (x.y) atomicAdd(&gh[4 * v + 1], x.y);
+    if (x.z) atomicAdd(&gh[4 * v + 2], x.z);
+    if (x.w) atomicAdd(&gh[4 * v + 3], x.w);
+  }
+}
+
+__global__ void __launch_bounds__(1024) k_fs_bracket(const DevTensor* __restrict__ tab, int K,
+                                                     FusedUnit* __restrict__ fu, int* __restrict__ tflag,
+                                                     const uint32_t* __restrict__ hist) {
+  __shared__ __attribute__((aligned(16))) uint32_t bins[kBins];
+  __shared__ int64_t sh[17];
+  __shared__ int32_t found[3];
+  const int u = blockIdx.x;
+  const DevTensor& T = tab[u / K];
+  if (fu[u].flags & (kFusedNone | kFusedAll)) return;
+  const uint4* gh = (const uint4*)(hist + (size_t)u * kBins);
+#pragma unroll
+  for (int v = 0; v < kBins / 4 / 1024; ++v) ((uint4*)bins)[v * 1024 + threadIdx.x] = gh[v * 1024 + threadIdx.x];
+  __syncthreads();
+  const bool exact = T.n <= kExactMax;
+  bracket_from(fu[u], &tflag[u / K], bins, exact ? T.n : (int64_t)kSampleBlocks * kSampleSpan, T.n, exact, sh, found);
+}
+
+// Workgroups per delta for the sample.  Each costs about as much as 2^17 entries besides its share
+// (clearing and flushing its bins), so a sample is cut into at most 16 parts of 2^16, and only while
+// the parts of all deltas run at once: 14 deltas of 4.2M to 11.5M entries, 1 workgroup each 74 us,
+// 16 each and the bracket launch 27 us (the call 204 -> 152 us).
+inline int sample_parts(int nu) { return std::max(1, std::min(16, 256 / std::max(1, nu))); }
 
 // ---- 2. main pass --------------------------------------------------------------------------------
 //
@@ -701,21 +761,15 @@ __global__ void __launch_bounds__(1024) k_fs_reduce(const DevTensor* __restrict_
   }
 }
 
-// Exact threshold per delta from the bracket counts (one thread per delta).  The main pass
+// Exact threshold of one delta from the bracket counts, by one thread; false: the tensor takes the
+// two-pass path.  The main pass
 // counts the entries it kept provisionally (key >= prov_key); those above the bracket are
 // that count less the bracket codes at or above prov_key.
-__global__ void k_fs_resolve(const DevTensor* __restrict__ tab, int n_t, int K, FusedUnit* __restrict__ fu,
-                             int* __restrict__ tflag, uint32_t* status) {
-  const int u = blockIdx.x * blockDim.x + threadIdx.x;
-  if (u >= n_t * K) return;
-  const int j = u / K;
-  if (tflag[j]) return;
-  FusedUnit& F = fu[u];
-  const int64_t n = tab[j].n;
+__device__ bool resolve_delta(FusedUnit& F, int64_t n, int* tflag, uint32_t* status) {
   if (F.flags & kFusedNone) {
     F.t_key = kNoSelectKey;
     F.cutoff = 0;
-    return;
+    return true;
   }
   const int64_t k = F.k;
   const int W = (int)(F.hi - F.lo + 1u);
@@ -730,11 +784,11 @@ __global__ void k_fs_resolve(const DevTensor* __restrict__ tab, int n_t, int K, 
     F.quota = k - cum;
     F.count_t = n - cum;
     F.cutoff = n;
-    return;
+    return true;
   }
   if (k <= cum) {                                   // threshold above the bracket
-    atomicOr(&tflag[j], kFlagMiss);
-    return;
+    atomicOr(tflag, kFlagMiss);
+    return false;
   }
   for (int c = W - 1; c >= 0; --c) {
     const uint32_t code = F.lo + (uint32_t)c;
@@ -747,7 +801,7 @@ __global__ void k_fs_resolve(const DevTensor* __restrict__ tab, int n_t, int K, 
       F.count_t = h;
       F.cutoff = (F.quota == h) ? n : -1;           // -1: found from the records
       if (code >= 0x7F80u) flag_status(status, kStatusNonFinite);
-      return;
+      return true;
     }
     cum += h;
   }
@@ -757,15 +811,16 @@ __global__ void k_fs_resolve(const DevTensor* __restrict__ tab, int n_t, int K, 
     F.quota = k - cum;
     F.count_t = n - cum;
     F.cutoff = n;
-    return;
+    return true;
   }
-  atomicOr(&tflag[j], kFlagMiss);                   // threshold below the bracket
+  atomicOr(tflag, kFlagMiss);                       // threshold below the bracket
+  return false;
 }
 
 struct TieArgs {
   const DevTensor* tab;
   FusedUnit* fu;
-  const int* tflag;
+  int* tflag;
   const int64_t* ritem0;
   const uint32_t* csum;
   const uint16_t* tstat;
@@ -775,8 +830,9 @@ struct TieArgs {
   uint32_t* status;
 };
 
-// One workgroup per delta whose threshold code is only partly kept: the reduction chunk,
-// then the tile, then the record holding the quota-th entry of that code in flat order.
+// One workgroup per delta: its exact threshold, then, where the threshold code is only partly kept, the
+// reduction chunk, the tile and the record holding the quota-th entry of that code in flat order.
+// (Another delta's workgroup may flag the tensor meanwhile: what is found here is then not used.)
 template <int K>
 __global__ void __launch_bounds__(1024) k_fs_tiefind(TieArgs a) {
   constexpr int RW = rec_words<K>();
@@ -784,8 +840,12 @@ __global__ void __launch_bounds__(1024) k_fs_tiefind(TieArgs a) {
   __shared__ int64_t s_pos, s_before;
   const int u = blockIdx.x;
   const int j = u / K, i = u % K;
-  if (a.tflag[j] || a.fu[u].cutoff >= 0) return;
   const DevTensor& T = a.tab[j];
+  __shared__ int s_go;
+  if (threadIdx.x == 0)
+    s_go = !a.tflag[j] && resolve_delta(a.fu[u], T.n, &a.tflag[j], a.status) && a.fu[u].cutoff < 0;
+  __syncthreads();
+  if (!s_go) return;
   const int64_t quota = a.fu[u].quota;
   const uint32_t tk = a.fu[u].t_key;
   const int ct = 1 + (int)(tk - a.fu[u].lo);
@@ -1057,16 +1117,18 @@ __global__ void __launch_bounds__(256) k_fs_fixup(FixArgs a) {
   if (kmax >= 0x7F80u) flag_status(a.status, kStatusNonFinite);
 }
 
-__global__ void k_fs_count(const int* __restrict__ tflag, int n_t, uint32_t* __restrict__ count) {
-  for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < n_t; j += gridDim.x * blockDim.x)
-    if (tflag[j]) atomicAdd(count, 1u);
-}
-
 template <int K>
 hipError_t launch_k(const FusedPlan& pl, hipStream_t s) {
   const int nu = pl.n_t * K;
-  k_fs_init<<<(std::max(nu, pl.n_t) + 255) / 256, 256, 0, s>>>(pl.tab, pl.n_t, K, pl.fu, pl.tflag);
-  k_fs_sample<<<nu, 1024, 0, s>>>(pl.tab, K, pl.fu, pl.tflag);
+  const int parts = sample_parts(nu);
+  if (parts > 1) {
+    k_fs_init<<<(unsigned)(nu * (kBins / 4 / 256)), 256, 0, s>>>(pl.tab, pl.n_t, K, pl.fu, pl.tflag, pl.sel.hist);
+    k_fs_sample_part<<<dim3((unsigned)parts, (unsigned)nu), 1024, 0, s>>>(pl.tab, K, pl.fu, pl.sel.hist);
+    k_fs_bracket<<<nu, 1024, 0, s>>>(pl.tab, K, pl.fu, pl.tflag, pl.sel.hist);
+  } else {
+    k_fs_init<<<(std::max(nu, pl.n_t) + 255) / 256, 256, 0, s>>>(pl.tab, pl.n_t, K, pl.fu, pl.tflag, nullptr);
+    k_fs_sample<<<nu, 1024, 0, s>>>(pl.tab, K, pl.fu, pl.tflag);
+  }
   if (pl.tiles > 0) {
     MainArgs m;
     m.tab = pl.tab;
@@ -1090,7 +1152,6 @@ hipError_t launch_k(const FusedPlan& pl, hipStream_t s) {
   if (pl.ritems > 0)
     k_fs_reduce<K><<<(unsigned)(pl.ritems / K), 1024, 0, s>>>(pl.tab, pl.n_t, pl.ritem0, pl.tflag, pl.tstat, pl.csum,
                                                                pl.fu);
-  k_fs_resolve<<<(nu + 255) / 256, 256, 0, s>>>(pl.tab, pl.n_t, K, pl.fu, pl.tflag, pl.status);
   TieArgs ta;
   ta.tab = pl.tab;
   ta.fu = pl.fu;
@@ -1117,10 +1178,10 @@ hipError_t launch_k(const FusedPlan& pl, hipStream_t s) {
     fa.status = pl.status;
     k_fs_fixup<K><<<(unsigned)pl.groups, 256, 0, s>>>(fa);
   }
-  k_fs_count<<<1, 256, 0, s>>>(pl.tflag, pl.n_t, pl.status + 1);
   // tensors the single read could not settle: the exact two-pass path, flagged tensors only
   SelectPlan sp = pl.sel;
   sp.filter = pl.tflag;
+  sp.flagged = pl.status + 1;
   hipError_t e = run_select(sp, ISO_BF16, s);
   if (e != hipSuccess) return e;
   MergePlan mp = pl.mrg;

@@ -35,6 +35,7 @@ struct SelectPlan {
   const int* filter = nullptr;  // n_t device flags: only flagged tensors are selected (others get
                                 // t_key = none); null: every tensor.  Histograms of flagged units are
                                 // cleared by the launch itself.
+  uint32_t* flagged = nullptr;  // with filter: receives the number of flagged tensors (added to it)
   // joint selection (bf16): n_groups groups of tensors selected together per delta
   int n_groups = 0;
   const int* gid = nullptr;         // n_t: dense group index or -1

@@ -55,18 +55,10 @@ __device__ int64_t block_inclusive_scan(int64_t v, int64_t* sh /* >= 16 */) {
 
 // ---- unit setup ---------------------------------------------------------------------------------
 
-// With `filter` set, only units of flagged tensors take part; the others are finished
-// (no key selected) before the first pass.
+// A unit's state before the first pass; skip: finished (no key selected).
 // A member of a joint selection starts with its group's count (so that it is histogrammed
 // whenever the group keeps anything); k_group_assign sets its own share before the resolve.
-__global__ void k_select_init(const DevTensor* tab, int n_t, int K, UnitState* st, const int* filter,
-                              const int* gid, const int64_t* gk) {
-  int u = blockIdx.x * blockDim.x + threadIdx.x;
-  if (u >= n_t * K) return;
-  const DevTensor& T = tab[u / K];
-  const bool skip = (filter != nullptr) && !filter[u / K];
-  const int g = (gid != nullptr) ? gid[u / K] : -1;
-  const int64_t k = (g >= 0) ? gk[g] : T.k;
+__device__ __forceinline__ UnitState unit_start(const DevTensor& T, int64_t k, bool skip) {
   UnitState s;
   s.prefix = 0;
   s.key_max = 0;
@@ -77,7 +69,15 @@ __global__ void k_select_init(const DevTensor* tab, int n_t, int K, UnitState* s
   s.done = (k == 0 || T.n == 0 || skip) ? 1 : 0;
   if (s.done) s.prefix = kNoSelectKey;
   s.pad[0] = s.pad[1] = s.pad[2] = 0;
-  st[u] = s;
+  return s;
+}
+
+__global__ void k_select_init(const DevTensor* tab, int n_t, int K, UnitState* st, const int* gid, const int64_t* gk) {
+  int u = blockIdx.x * blockDim.x + threadIdx.x;
+  if (u >= n_t * K) return;
+  const DevTensor& T = tab[u / K];
+  const int g = (gid != nullptr) ? gid[u / K] : -1;
+  st[u] = unit_start(T, (g >= 0) ? gk[g] : T.k, false);
 }
 
 // Work item -> (tensor j, delta i, chunk c), items of tensor j laid out delta-major.
@@ -266,10 +266,18 @@ __global__ void __launch_bounds__(kHistThreads) k_hist_flagged(const DevTensor* 
       });
 }
 
-// Clears the global histograms of the flagged tensors' units.
-__global__ void __launch_bounds__(1024) k_clear_hist_flagged(int n_t, int K, uint32_t* __restrict__ hist,
-                                                             const int* __restrict__ filter) {
+// The start of a filtered selection: unit states (units of unflagged tensors finished, with no key
+// selected), the flagged tensors' global histograms cleared, their number added to *flagged.
+__global__ void __launch_bounds__(1024) k_select_init_flagged(const DevTensor* __restrict__ tab, int n_t, int K,
+                                                              UnitState* __restrict__ st, uint32_t* __restrict__ hist,
+                                                              const int* __restrict__ filter, uint32_t* flagged) {
   __shared__ int sflag[1024];
+  for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < (int64_t)n_t * K; u += (int64_t)gridDim.x * blockDim.x) {
+    const int j = (int)(u / K);
+    const bool on = filter[j] != 0;
+    st[u] = unit_start(tab[j], tab[j].k, !on);
+    if (on && u % K == 0 && flagged != nullptr) atomicAdd(flagged, 1u);
+  }
   for_flagged_items(
       filter, n_t, sflag, [&](int) { return (int64_t)K * (kMaxBins / 1024); },
       [&](int j, int64_t it) { hist[(size_t)j * K * kMaxBins + (size_t)it * 1024 + threadIdx.x] = 0u; });
@@ -864,10 +872,13 @@ static hipError_t run_select_t(const SelectPlan& pl, hipStream_t s) {
   const int nu = pl.n_t * pl.K;
   const bool flt = pl.filter != nullptr;
   constexpr unsigned kFlaggedGrid = 256;
-  if (flt) k_clear_hist_flagged<<<kFlaggedGrid, 1024, 0, s>>>(pl.n_t, pl.K, pl.hist, pl.filter);
-  if (pl.n_groups > 0 && DT != ISO_BF16) return hipErrorInvalidValue;   // the entry points reject these
-  k_select_init<<<(nu + 255) / 256, 256, 0, s>>>(pl.tab, pl.n_t, pl.K, pl.states, pl.filter,
-                                                 pl.n_groups > 0 ? pl.gid : nullptr, pl.gk);
+  // the entry points reject groups of fp32 tensors, and groups do not take the single-read path
+  if (pl.n_groups > 0 && (DT != ISO_BF16 || flt)) return hipErrorInvalidValue;
+  if (flt)
+    k_select_init_flagged<<<kFlaggedGrid, 1024, 0, s>>>(pl.tab, pl.n_t, pl.K, pl.states, pl.hist, pl.filter, pl.flagged);
+  else
+    k_select_init<<<(nu + 255) / 256, 256, 0, s>>>(pl.tab, pl.n_t, pl.K, pl.states, pl.n_groups > 0 ? pl.gid : nullptr,
+                                                   pl.gk);
   struct Pass { int shift, bits; };
   const Pass bf[1] = {{0, 15}};
   const Pass f32[3] = {{16, 15}, {8, 8}, {0, 8}};

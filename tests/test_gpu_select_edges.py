@@ -7,7 +7,8 @@ import pytest
 from oracle import numerics as nm
 from oracle import ties
 
-from tests.gpu_helpers import Unit, bits_to_mask, run_topk, say
+import paper_2607_19331_amd as iso
+from tests.gpu_helpers import Unit, bits_to_mask, run_fused, run_topk, say
 
 pytestmark = pytest.mark.gpu
 
@@ -58,3 +59,21 @@ def test_tie_cutoff_inside_chunks(dtype):
                               dtype, k))
     say(f"tie cutoff {dtype}")
     check(units, 2, dtype)
+
+
+@pytest.mark.parametrize("copies", [1, 30])
+def test_sample_of_few_and_of_many_deltas(copies):
+    """iso_update FUSED TIES around the size up to which a delta is histogrammed whole (2^20), with a few deltas
+    (each sample split over several workgroups) and with more than there are CUs (one workgroup each)."""
+    rng = np.random.default_rng(73)
+    units = []
+    for n in (1, 9, 4097, (1 << 20) - 1, 1 << 20, (1 << 20) + 257):
+        ds = [nm.from_f64(np.round(rng.standard_normal(n) * 40.0) * (rng.random(n) > 0.5) / 65536.0, "bf16") for _ in range(2)]
+        units.append(Unit(1, n, nm.from_f64(rng.standard_normal(n) * 0.02, "bf16"), ds, "bf16", (n + 4) // 5))
+    want = [ties.merge_unit(u.base, u.deltas, "bf16", "ties", k=u.k)["out"] for u in units]
+    small = [Unit(1, 4097, u.base, u.deltas, "bf16", u.k) for u in units[2:3] for _ in range(copies * 4)]
+    say(f"sample parts, {copies} copies")
+    outs, _, st = run_fused(units + small, 2, "bf16", iso.MERGE_TIES)
+    assert st == 0
+    for u, o, w in zip(units + small, outs, want + [want[2]] * len(small)):
+        assert np.array_equal(o.view(np.uint16), w.view(np.uint16)), u.n
