@@ -146,7 +146,7 @@ typedef struct iso_tensor {
  * whole count on one member or spread it).  The descriptors stay per tensor
  * and per delta, each describing that tensor's part of the joint mask (its
  * n_above + tie_quota is its share of K_g).  bf16 only (ISO_ERR_UNSUPPORTED
- * for an fp32 call with a group); calls with groups take the two-pass path.
+ * for an fp32 call with a group).
  */
 typedef struct iso_select_desc {
   uint32_t t_key;
@@ -224,7 +224,10 @@ typedef struct iso_update_args {
  *            coordinates with a key inside the bracket are logged and fixed up
  *            once the exact threshold is known.  A tensor whose threshold the
  *            bracket misses takes the two-pass path on the device; the result
- *            is the same (iso_read_fallback_count reports how many did).
+ *            is the same (iso_read_fallback_count reports how many did); a
+ *            group goes as one.  Calls with groups take the two-pass path below
+ *            2^26 coordinates, where an output overlaps an input of its tensor,
+ *            and in a workspace of ISO_OP_TOPK's size for the table.
  *  SPECTRAL: ISO-Merger, Sec. 4.2 / App. E / Algorithm 1, per matrix, in
  *            binary64: SVDs of W_0 and W_i = W_0 + tau_i, joint sign
  *            canonicalisation, tangent projection, D_keep, effect proxies and

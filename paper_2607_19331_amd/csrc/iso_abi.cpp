@@ -72,11 +72,12 @@ iso_status check_ptr_array(const void* const* p, int n, bool required) {
 }
 
 // Joint-selection groups of a table: dense group index per tensor (-1 alone), members of each
-// group in table order, the group's count (sum of its members' k) and size.
+// group in table order, the group's count (sum of its members' k) and size, and its members' sample
+// blocks (whole ones; numbered through the group in table order).
 struct GroupMap {
   int n = 0;
   std::vector<int> gid, mem, mem0;
-  std::vector<int64_t> gk, gn;
+  std::vector<int64_t> gk, gn, gnb, blk0;
 };
 
 GroupMap group_map(const iso_tensor* t, int n_t) {
@@ -93,6 +94,8 @@ GroupMap group_map(const iso_tensor* t, int n_t) {
   G.mem0.assign(G.n + 1, 0);
   G.gk.assign(G.n, 0);
   G.gn.assign(G.n, 0);
+  G.gnb.assign(G.n, 0);
+  G.blk0.assign(n_t, 0);
   for (int j = 0; j < n_t; ++j)
     if (G.gid[j] >= 0) {
       G.mem0[G.gid[j] + 1] += 1;
@@ -100,6 +103,8 @@ GroupMap group_map(const iso_tensor* t, int n_t) {
       const __int128 sum = (__int128)G.gk[G.gid[j]] + t[j].k;
       G.gk[G.gid[j]] = sum > (__int128)INT64_MAX ? INT64_MAX : (int64_t)sum;
       G.gn[G.gid[j]] += t[j].rows * t[j].cols;
+      G.blk0[j] = G.gnb[G.gid[j]];
+      G.gnb[G.gid[j]] += t[j].rows * t[j].cols / fused_sample_span();
     }
   for (int g = 0; g < G.n; ++g) G.mem0[g + 1] += G.mem0[g];
   G.mem.assign(G.mem0[G.n], 0);
@@ -126,7 +131,7 @@ struct Layout {
   size_t states = 0, hist = 0, tiecnt = 0, desc = 0, chunk_hist = 0;
   size_t fu = 0, tflag = 0, tstat = 0, tinfo = 0, csum = 0, rec = 0;
   size_t spectral = 0;
-  size_t ggid = 0, gmem = 0, gmem0 = 0, gk = 0, ghist = 0, gstate = 0, mcnt = 0;
+  size_t ggid = 0, gmem = 0, gmem0 = 0, gk = 0, gn = 0, gnb = 0, gblk0 = 0, ghist = 0, gstate = 0, mcnt = 0;
   int n_groups = 0;
   size_t total = 0;
   int64_t hist_chunk = 0, hist_items = 0, tie_items = 0, tiles = 0, groups = 0, ritems = 0, tile_cap = 0;
@@ -138,7 +143,29 @@ bool fused_eligible(int op, int n_t, int dt) {
   return op == ISO_OP_UPDATE_FUSED_SELECT && dt == ISO_BF16 && n_t <= kFusedMaxTensors;
 }
 
-Layout plan(int op, const iso_tensor* t, int n_t, int K, int dt) {
+// Joint selections take it from this many coordinates in the call.  The two-pass path's launches cost
+// less below (K = 8: 2^21 coordinates 120 against 175 us, 2^24 240 against 240); at 2^26 one read
+// takes K = 1: 144 against 185 us, K = 2: 179 / 234, K = 4: 260 / 349, K = 8: 457 / 568, at 2^27 four
+// deltas 393 against 576.  A group of few distinct magnitudes is given up after its sample and then
+// costs 40 to 150 us more than two passes alone, which the line keeps a small share.
+constexpr int64_t kFusedGroupMin = 1ll << 26;
+
+// Whether a merged weight may be written over an input of its tensor.  The two-pass merge reads an
+// entry's inputs before it writes the entry and never after; the single read may come back to them.
+bool writes_inputs(const iso_tensor* t, int n_t, int K, int dt) {
+  const uintptr_t size = (dt == ISO_BF16) ? 2 : 4;
+  for (int j = 0; j < n_t; ++j) {
+    const uintptr_t bytes = size * (uintptr_t)(t[j].rows * t[j].cols), o = (uintptr_t)t[j].out;
+    for (int i = -1; i < K; ++i) {
+      const uintptr_t p = (uintptr_t)(i < 0 ? t[j].base : t[j].deltas[i]);
+      if (p < o + bytes && o < p + bytes) return true;
+    }
+  }
+  return false;
+}
+
+// joint_single: joint selections may take the single-read path.
+Layout plan(int op, const iso_tensor* t, int n_t, int K, int dt, bool joint_single = true) {
   Layout L;
   size_t off = kStatusBytes;
   L.table = off;
@@ -168,12 +195,20 @@ Layout plan(int op, const iso_tensor* t, int n_t, int K, int dt) {
       off = align_up(off + sizeof(int) * (size_t)(G.n + 1), 256);
       L.gk = off;
       off = align_up(off + sizeof(int64_t) * (size_t)G.n, 256);
+      L.gn = off;
+      off = align_up(off + sizeof(int64_t) * (size_t)G.n, 256);
+      L.gnb = off;
+      off = align_up(off + sizeof(int64_t) * (size_t)G.n, 256);
+      L.gblk0 = off;
+      off = align_up(off + sizeof(int64_t) * (size_t)n_t, 256);
     }
   }
   L.upload_end = off;
-  L.fused = fused_eligible(op, n_t, dt) && L.n_groups == 0;
+  int64_t entries = 0;
+  for (int j = 0; j < n_t; ++j) entries += t[j].rows * t[j].cols;
+  L.fused = fused_eligible(op, n_t, dt) && (L.n_groups == 0 || (joint_single && entries >= kFusedGroupMin));
   if (L.select) {
-    L.hist_chunk = hist_chunk_for(t, n_t, K, dt, L.fused);
+    L.hist_chunk = hist_chunk_for(t, n_t, K, dt, L.fused && L.n_groups == 0);
     for (int j = 0; j < n_t; ++j) {
       const int64_t n = t[j].rows * t[j].cols;
       L.hist_items += K * ((n + L.hist_chunk - 1) / L.hist_chunk);
@@ -306,6 +341,9 @@ hipError_t upload(const Layout& L, const iso_tensor* t, int n_t, int K, int dt, 
     if (!G.mem.empty()) std::memcpy(h + (L.gmem - L.table), G.mem.data(), sizeof(int) * G.mem.size());
     std::memcpy(h + (L.gmem0 - L.table), G.mem0.data(), sizeof(int) * G.mem0.size());
     std::memcpy(h + (L.gk - L.table), G.gk.data(), sizeof(int64_t) * G.gk.size());
+    std::memcpy(h + (L.gn - L.table), G.gn.data(), sizeof(int64_t) * G.gn.size());
+    std::memcpy(h + (L.gnb - L.table), G.gnb.data(), sizeof(int64_t) * G.gnb.size());
+    std::memcpy(h + (L.gblk0 - L.table), G.blk0.data(), sizeof(int64_t) * (size_t)n_t);
   }
   // coarse tile map: the last tensor whose first tile is at or before m << kTileMapShift
   int* tm = (int*)(h + (L.tmap - L.table));
@@ -398,7 +436,8 @@ size_t iso_workspace_size(int op, const iso_tensor* t, int n_t, int K, int dt) {
   for (int j = 0; j < n_t; ++j)
     if (t[j].rows < 0 || t[j].cols < 0) return 0;
   if (op == ISO_OP_BLOCKDIAG) return 0;
-  return plan(op, t, n_t, K, dt).total;
+  // with joint selections either path may run (see iso_update)
+  return std::max(plan(op, t, n_t, K, dt).total, plan(op, t, n_t, K, dt, false).total);
 }
 
 iso_status iso_topk_mask(const iso_tensor* t, int n_t, int K, int dt, iso_select_desc* desc,
@@ -544,8 +583,14 @@ iso_status update_call(const iso_tensor* t, int n_t, int K, int dt, const iso_up
     const bool want_sign = ties && a->sign_out != nullptr;
     if (want_sign && (st = check_ptr_array((const void* const*)a->sign_out, n_t, true)) != ISO_OK) return st;
     const bool inner_select = ties && a->desc == nullptr;
-    Layout L = plan(inner_select ? ISO_OP_UPDATE_FUSED_SELECT : ISO_OP_UPDATE_FUSED, t, n_t, K, dt);
-    if ((st = take_ws(src, L, &w)) != ISO_OK) return st;
+    const int op = inner_select ? ISO_OP_UPDATE_FUSED_SELECT : ISO_OP_UPDATE_FUSED;
+    Layout L = plan(op, t, n_t, K, dt, inner_select && !writes_inputs(t, n_t, K, dt));
+    st = take_ws(src, L, &w);
+    if (st != ISO_OK && L.fused && L.n_groups > 0) {   // joint selections in a workspace for two passes only
+      L = plan(op, t, n_t, K, dt, false);
+      st = take_ws(src, L, &w);
+    }
+    if (st != ISO_OK) return st;
     HIP_TRY(start_call(w, s));
     HIP_TRY(upload(L, t, n_t, K, dt, w, nullptr, want_sign ? (void* const*)a->sign_out : nullptr, nullptr, 0, s));
     MergePlan mp;
@@ -581,6 +626,16 @@ iso_status update_call(const iso_tensor* t, int n_t, int K, int dt, const iso_up
       fp.want_sign = want_sign ? 1 : 0;
       fp.status = (uint32_t*)w;
       fp.sel = select_plan(L, w, n_t, K, dd);
+      if (L.n_groups > 0) {
+        fp.grp.gid = fp.sel.gid;
+        fp.grp.gmem = fp.sel.gmem;
+        fp.grp.gmem0 = fp.sel.gmem0;
+        fp.grp.gk = fp.sel.gk;
+        fp.grp.gn = (const int64_t*)(w + L.gn);
+        fp.grp.gnb = (const int64_t*)(w + L.gnb);
+        fp.grp.blk0 = (const int64_t*)(w + L.gblk0);
+        fp.grp.n_groups = L.n_groups;
+      }
       fp.mrg = mp;
       if (!src.acquire) prof_take(fp.prof);
       HIP_TRY(run_fused(fp, s));

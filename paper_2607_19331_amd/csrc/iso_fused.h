@@ -24,7 +24,7 @@ struct FusedUnit {
   uint32_t lo, hi, prov;   // bracket [lo, hi] of magnitude keys and the provisional threshold
   uint32_t flags;          // kFused* below
   uint32_t t_key;          // exact threshold key (kNoSelectKey: nothing kept)
-  uint32_t pad;
+  uint32_t share;          // first delta of a group's first member: its brackets' share of the samples, in 2^-20
   int64_t k;
   uint64_t kept;           // entries the main pass kept provisionally (key >= max(prov, 1))
   int64_t n_above, quota, count_t;
@@ -34,6 +34,19 @@ struct FusedUnit {
 
 constexpr uint32_t kFusedNone = 1u;   // k == 0
 constexpr uint32_t kFusedAll = 2u;    // k == n
+
+// Joint selections of a call as the single-read kernels see them (gid null: none).  A group's sample
+// is drawn from the 256-entry blocks of its members, numbered through in table order.
+struct FusedGroups {
+  const int* gid = nullptr;         // n_t: dense group index or -1
+  const int* gmem = nullptr;        // members of every group, in table order
+  const int* gmem0 = nullptr;       // n_groups + 1 offsets into gmem (no group is empty)
+  const int64_t* gk = nullptr;      // n_groups: entries a group keeps per delta
+  const int64_t* gn = nullptr;      // n_groups: entries of a group
+  const int64_t* gnb = nullptr;     // n_groups: blocks of a group
+  const int64_t* blk0 = nullptr;    // n_t: first block of a member in its group
+  int n_groups = 0;
+};
 
 struct FusedPlan {
   const DevTensor* tab;
@@ -52,12 +65,14 @@ struct FusedPlan {
   double lambda;
   int want_sign;           // .aux2 of the table holds the int8 sign output
   uint32_t* status;        // status block; word 1 receives the number of tensors that took the two-pass path
+  FusedGroups grp;
   SelectPlan sel;          // exact two-pass path (its filter is set to tflag by the launcher)
   MergePlan mrg;
   hipEvent_t prof[2] = {nullptr, nullptr};   // recorded around the main pass when set
 };
 
 int64_t fused_tile_elems();
+int64_t fused_sample_span();       // entries of one sampled block
 int64_t fused_groups(int64_t n);   // fix-up runs of a tensor of n entries (tensors never share one)
 int64_t fused_reduce_items(int64_t n, int K);
 size_t fused_record_bytes(int K);

@@ -19,7 +19,9 @@
 //      and rewritten where the result changes.
 // A threshold outside its bracket (a misleading sample), a bracket wider than kFusedMaxW
 // codes or a full record region sends the tensor to the exact two-pass path (histogram
-// select, then merge) on the same stream; the result is identical either way.  Zero keys
+// select, then merge) on the same stream; the result is identical either way.  Tensors selected
+// jointly share one sample and one bracket per delta, their counts are added before the resolve, the
+// tie quota goes to the members in table order, and one member on the two-pass path takes its group.  Zero keys
 // need no decision: a kept zero adds nothing to the election or to the mean.
 #include <algorithm>
 
@@ -47,6 +49,12 @@ __device__ __forceinline__ uint32_t bkey(uint32_t b) { return b & 0x7FFFu; }
 
 template <int K>
 constexpr int kTileCapK = (K <= 4) ? (int)(kTileElems / 16) : (int)(kTileElems / 8);   // records per tile
+
+// Share of a tile's coordinates (in 2^-20) that its record area holds with five standard deviations to spare.
+__device__ __forceinline__ uint32_t record_share_limit(int K) {
+  const float cap = (float)((K <= 4) ? kTileCapK<4> : kTileCapK<8>);
+  return (uint32_t)((cap - 5.0f * sqrtf(cap)) * (1048576.0f / (float)kTileElems));
+}
 
 template <int K>
 constexpr int rec_words() {
@@ -81,23 +89,35 @@ __device__ int64_t block_scan(int64_t v, int64_t* sh /* >= 17 */) {
 
 // ---- 0. per-call state -------------------------------------------------------------------------
 
+__device__ __forceinline__ int group_of(const FusedGroups& G, int j) { return (G.gid != nullptr) ? G.gid[j] : -1; }
+
+// The tensor whose slots hold the sample histograms of j's selection: its group's first member, or j.
+__device__ __forceinline__ int sample_slot(const FusedGroups& G, int j) {
+  const int g = group_of(G, j);
+  return (g < 0) ? j : G.gmem[G.gmem0[g]];
+}
+
 // hist: the units' sample histograms, cleared when the sample is split (else null).
 __global__ void k_fs_init(const DevTensor* __restrict__ tab, int n_t, int K, FusedUnit* __restrict__ fu,
-                          int* __restrict__ tflag, uint32_t* __restrict__ hist) {
+                          int* __restrict__ tflag, uint32_t* __restrict__ hist, FusedGroups G) {
   const int u = blockIdx.x * blockDim.x + threadIdx.x;
   if (hist != nullptr)
-    for (int64_t v = u; v < (int64_t)n_t * K * (kBins / 4); v += (int64_t)gridDim.x * blockDim.x)
-      ((uint4*)hist)[v] = make_uint4(0, 0, 0, 0);
+    for (int64_t v = u; v < (int64_t)n_t * K * (kBins / 4); v += (int64_t)gridDim.x * blockDim.x) {
+      const int j = (int)(v / ((int64_t)K * (kBins / 4)));
+      if (sample_slot(G, j) == j) ((uint4*)hist)[v] = make_uint4(0, 0, 0, 0);
+    }
   if (u < n_t) tflag[u] = 0;
   if (u >= n_t * K) return;
   const DevTensor& T = tab[u / K];
+  const int g = group_of(G, u / K);
+  const int64_t k = (g < 0) ? T.k : G.gk[g];
   FusedUnit f;
-  f.flags = (T.k == 0) ? kFusedNone : ((T.k == T.n) ? kFusedAll : 0u);
+  f.flags = (k == 0) ? kFusedNone : ((k == ((g < 0) ? T.n : G.gn[g])) ? kFusedAll : 0u);
   if (f.flags & kFusedNone) f.lo = f.hi = f.prov = 0x8000u;   // above every key: nothing kept
   else f.lo = f.hi = f.prov = 0u;                            // k == n: every nonzero key is above
   f.t_key = 0;
-  f.pad = 0;
-  f.k = T.k;
+  f.share = 0;
+  f.k = k;
   f.kept = 0;
   f.n_above = f.quota = f.count_t = 0;
   f.cutoff = T.n;
@@ -107,10 +127,38 @@ __global__ void k_fs_init(const DevTensor* __restrict__ tab, int n_t, int K, Fus
 
 // ---- 1. sample and bracket ---------------------------------------------------------------------
 
-// Part `part` of `parts` of a delta's sample into the block's LDS histogram (cleared here); returns
-// the entries of the whole sample.  Two costs per part: the clearing of 128 KB of bins, then loads and LDS
+// What one tensor adds to the sample of its selection (itself, or its group).
+struct SampleShare {
+  bool whole;          // the selection holds at most kExactMax entries: all of them are counted
+  int64_t n, ns;       // entries of the selection and of its whole sample
+  int64_t nb, blk0;    // blocks of the selection, and the tensor's first among them
+  int64_t s;           // blocks sampled: block b of the sample is block floor(b * nb / s) of the selection
+  int64_t b0, b1;      // those that fall into the tensor
+};
+
+// s <= nb, so the sampled blocks are distinct; floor(b * nb / s) >= x is b >= ceil(x * s / nb).
+__device__ __forceinline__ SampleShare sample_share(const DevTensor& T, const FusedGroups& G, int j) {
+  const int g = group_of(G, j);
+  SampleShare h;
+  h.n = (g < 0) ? T.n : G.gn[g];
+  h.nb = (g < 0) ? T.n / kSampleSpan : G.gnb[g];
+  h.blk0 = (g < 0) ? 0 : G.blk0[j];
+  h.whole = h.n <= kExactMax;
+  h.s = min<int64_t>(kSampleBlocks, h.nb);
+  h.ns = h.whole ? h.n : h.s * kSampleSpan;
+  h.b0 = h.b1 = 0;
+  if (h.nb > 0) {
+    h.b0 = (h.blk0 * h.s + h.nb - 1) / h.nb;
+    h.b1 = ((h.blk0 + T.n / kSampleSpan) * h.s + h.nb - 1) / h.nb;
+  }
+  return h;
+}
+
+// Part `part` of `parts` of a tensor's share of the sample of delta i into the block's LDS histogram
+// (cleared here).  Two costs per part: the clearing of 128 KB of bins, then loads and LDS
 // atomics at one CU's rate (a whole sample of 2^20 entries takes one workgroup 70 us).
-__device__ __forceinline__ int64_t sample_part(const DevTensor& T, int i, int part, int parts, uint32_t* bins) {
+__device__ __forceinline__ void sample_part(const DevTensor& T, const SampleShare& h, int i, int part, int parts,
+                                            uint32_t* bins) {
   for (int b = threadIdx.x; b < kBins / 4; b += blockDim.x) ((uint4*)bins)[b] = make_uint4(0, 0, 0, 0);
   __syncthreads();
   const int64_t n = T.n;
@@ -127,7 +175,7 @@ __device__ __forceinline__ int64_t sample_part(const DevTensor& T, int i, int pa
   // kInFlight 16-byte loads per thread before any is counted: one workgroup per CU (the
   // histogram takes 128 KB of LDS), so the loads in flight set the rate
   constexpr int kInFlight = 16;
-  if (n <= kExactMax) {
+  if (h.whole) {
     const int64_t nvec = n / 8, v1 = nvec * (part + 1) / parts;
     for (int64_t v = nvec * part / parts + threadIdx.x; v < v1; v += kInFlight * (int64_t)blockDim.x) {
       uint4 a[kInFlight];
@@ -146,22 +194,20 @@ __device__ __forceinline__ int64_t sample_part(const DevTensor& T, int i, int pa
         if (k) atomicAdd(&bins[k], 1u);
       }
     }
-    return n;
+    return;
   }
-  // block b starts at entry floor(b * nb / kSampleBlocks) * kSampleSpan, nb = n / kSampleSpan
-  // (n > kExactMax, so the blocks are distinct); 32 threads, one 16-byte vector each, per block
-  const int64_t nb = n / kSampleSpan;
+  // 32 threads, one 16-byte vector each, per block
   constexpr int kVecPerBlock = kSampleSpan / 8;
   const int per_iter = blockDim.x / kVecPerBlock;
   const int lb = threadIdx.x / kVecPerBlock, lv = threadIdx.x % kVecPerBlock;
-  const int b1 = kSampleBlocks * (part + 1) / parts;
-  for (int b0 = kSampleBlocks * part / parts; b0 < b1; b0 += kInFlight * per_iter) {
+  const int b1 = (int)(h.b0 + (h.b1 - h.b0) * (part + 1) / parts);
+  for (int b0 = (int)(h.b0 + (h.b1 - h.b0) * part / parts); b0 < b1; b0 += kInFlight * per_iter) {
     uint4 a[kInFlight];
 #pragma unroll
     for (int q = 0; q < kInFlight; ++q) {
       const int b = b0 + q * per_iter + lb;
       if (b < b1) {
-        const int64_t blk = (int64_t)b * nb / kSampleBlocks;
+        const int64_t blk = (int64_t)b * h.nb / h.s - h.blk0;
         a[q] = ld_stream(pv + blk * kVecPerBlock + lv);
       } else {
         a[q] = make_uint4(0, 0, 0, 0);
@@ -170,7 +216,6 @@ __device__ __forceinline__ int64_t sample_part(const DevTensor& T, int i, int pa
 #pragma unroll
     for (int q = 0; q < kInFlight; ++q) count8(a[q]);
   }
-  return (int64_t)kSampleBlocks * kSampleSpan;
 }
 
 // Bracket of unit u from the sample's histogram in LDS (ns entries sampled of n; exact: all of them).
@@ -227,7 +272,7 @@ __device__ void bracket_from(FusedUnit& F, int* tflag, const uint32_t* bins, int
   }
 }
 
-// One workgroup per delta: calls with enough deltas to fill the chip.
+// One workgroup per delta: calls with enough deltas to fill the chip and no joint selection.
 __global__ void __launch_bounds__(1024) k_fs_sample(const DevTensor* __restrict__ tab, int K,
                                                     FusedUnit* __restrict__ fu, int* __restrict__ tflag) {
   __shared__ __attribute__((aligned(16))) uint32_t bins[kBins];
@@ -236,21 +281,28 @@ __global__ void __launch_bounds__(1024) k_fs_sample(const DevTensor* __restrict_
   const int u = blockIdx.x;
   const DevTensor& T = tab[u / K];
   if (fu[u].flags & (kFusedNone | kFusedAll)) return;
-  const int64_t ns = sample_part(T, u % K, 0, 1, bins);
+  const SampleShare h = sample_share(T, FusedGroups(), u / K);
+  sample_part(T, h, u % K, 0, 1, bins);
   __syncthreads();
-  bracket_from(fu[u], &tflag[u / K], bins, ns, T.n, T.n <= kExactMax, sh, found);
+  bracket_from(fu[u], &tflag[u / K], bins, h.ns, T.n, h.whole, sh, found);
 }
 
-// Fewer deltas than CUs: each delta's sample split over gridDim.x workgroups that add their nonzero
-// bins to the delta's global histogram, then one workgroup per delta for the bracket.
+// Fewer deltas than CUs, or joint selections: each delta's share of its sample split over gridDim.x
+// workgroups that add their nonzero bins to the selection's global histogram, then one workgroup per
+// selection and delta for the bracket (the same for every member).
 __global__ void __launch_bounds__(1024) k_fs_sample_part(const DevTensor* __restrict__ tab, int K,
-                                                         const FusedUnit* __restrict__ fu, uint32_t* __restrict__ hist) {
+                                                         const FusedUnit* __restrict__ fu, uint32_t* __restrict__ hist,
+                                                         FusedGroups G) {
   __shared__ __attribute__((aligned(16))) uint32_t bins[kBins];
-  const int u = blockIdx.y;
+  const int parts = gridDim.y, part = blockIdx.y;
+  const int u = blockIdx.x, j = u / K;
   if (fu[u].flags & (kFusedNone | kFusedAll)) return;
-  sample_part(tab[u / K], u % K, blockIdx.x, gridDim.x, bins);
+  const SampleShare h = sample_share(tab[j], G, j);
+  const int64_t nblk = h.b1 - h.b0;              // a part without a block has nothing to add
+  if (h.whole ? tab[j].n == 0 : nblk * part / parts == nblk * (part + 1) / parts) return;
+  sample_part(tab[j], h, u % K, part, parts, bins);
   __syncthreads();
-  uint32_t* gh = hist + (size_t)u * kBins;
+  uint32_t* gh = hist + ((size_t)sample_slot(G, j) * K + u % K) * kBins;
   for (int v = threadIdx.x; v < kBins / 4; v += blockDim.x) {
     const uint4 x = ((const uint4*)bins)[v];
     if (x.x) atomicAdd(&gh[4 * v], x.x);
@@ -262,19 +314,42 @@ __global__ void __launch_bounds__(1024) k_fs_sample_part(const DevTensor* __rest
 
 __global__ void __launch_bounds__(1024) k_fs_bracket(const DevTensor* __restrict__ tab, int K,
                                                      FusedUnit* __restrict__ fu, int* __restrict__ tflag,
-                                                     const uint32_t* __restrict__ hist) {
+                                                     const uint32_t* __restrict__ hist, FusedGroups G) {
   __shared__ __attribute__((aligned(16))) uint32_t bins[kBins];
   __shared__ int64_t sh[17];
   __shared__ int32_t found[3];
-  const int u = blockIdx.x;
-  const DevTensor& T = tab[u / K];
-  if (fu[u].flags & (kFusedNone | kFusedAll)) return;
+  const int u = blockIdx.x, j = u / K;
+  if ((fu[u].flags & (kFusedNone | kFusedAll)) || sample_slot(G, j) != j) return;
   const uint4* gh = (const uint4*)(hist + (size_t)u * kBins);
 #pragma unroll
   for (int v = 0; v < kBins / 4 / 1024; ++v) ((uint4*)bins)[v * 1024 + threadIdx.x] = gh[v * 1024 + threadIdx.x];
   __syncthreads();
-  const bool exact = T.n <= kExactMax;
-  bracket_from(fu[u], &tflag[u / K], bins, exact ? T.n : (int64_t)kSampleBlocks * kSampleSpan, T.n, exact, sh, found);
+  const SampleShare h = sample_share(tab[j], G, j);
+  bracket_from(fu[u], &tflag[j], bins, h.ns, h.n, h.whole, sh, found);
+  const int g = group_of(G, j);
+  if (g < 0) return;
+  __syncthreads();                               // fu[u] is the block's own write
+  const uint32_t lo = fu[u].lo, hi = fu[u].hi, prov = fu[u].prov;
+  int reason = (hi - lo + 1u > (uint32_t)kFusedMaxW) ? kFlagWide : 0;
+  // Entries that share few magnitudes fill the tiles' record areas whatever the bracket.  The deltas'
+  // brackets' shares of the sample (in 2^-20) are added up in the first one's state; past what leaves a
+  // tile's area five standard deviations, the group goes to two passes before the main pass has read it.
+  __shared__ int s_full;
+  if (threadIdx.x == 0) {
+    uint32_t in = 0;
+    for (uint32_t c = max(lo, 1u); c <= hi && c < lo + kFusedMaxW; ++c) in += bins[c];
+    const uint32_t share = (uint32_t)(((uint64_t)in << 20) / (uint64_t)max<int64_t>(h.ns, 1));
+    s_full = atomicAdd(&fu[j * K].share, share) + share > record_share_limit(K);
+  }
+  __syncthreads();
+  if (s_full) reason |= kFlagFull;
+  for (int m = G.gmem0[g] + threadIdx.x; m < G.gmem0[g + 1]; m += blockDim.x) {
+    FusedUnit& F = fu[G.gmem[m] * K + u % K];
+    F.lo = lo;
+    F.hi = hi;
+    F.prov = prov;
+    if (reason) atomicOr(&tflag[G.gmem[m]], reason);
+  }
 }
 
 // Workgroups per delta for the sample.  Each costs about as much as 2^17 entries besides its share
@@ -420,6 +495,7 @@ struct MainArgs {
   int n_t;
   const FusedUnit* fu;
   int* tflag;
+  const int* early;        // tflag where the call has joint selections, else null
   uint16_t* tstat;
   uint32_t one2;           // 0x00010001, passed in so that min(d, 1) stays one packed min
   uint2* tinfo;
@@ -448,6 +524,7 @@ k_fs_main(MainArgs a) {
   __shared__ int s_skip, s_redo;
   const int64_t tile = blockIdx.x;
   const int j = find_tensor_mapped(a.tab, a.tmap, a.n_t, tile);
+  if (a.early != nullptr && a.early[j]) return;     // uniform; a group given up by its sample is not read
   const DevTensor& T = a.tab[j];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   // the stream loads first: nothing below delays their issue
@@ -761,60 +838,123 @@ __global__ void __launch_bounds__(1024) k_fs_reduce(const DevTensor* __restrict_
   }
 }
 
-// Exact threshold of one delta from the bracket counts, by one thread; false: the tensor takes the
-// two-pass path.  The main pass
+// Exact threshold of one selection and delta from its bracket counts, by one thread; false: it takes
+// the two-pass path.  The main pass
 // counts the entries it kept provisionally (key >= prov_key); those above the bracket are
-// that count less the bracket codes at or above prov_key.
-__device__ bool resolve_delta(FusedUnit& F, int64_t n, int* tflag, uint32_t* status) {
-  if (F.flags & kFusedNone) {
-    F.t_key = kNoSelectKey;
-    F.cutoff = 0;
-    return true;
-  }
+// that count less the bracket codes at or above prov_key.  n, kept, h: entries, provisionally kept
+// entries and bracket counts of the selection (one tensor, or the sums over a group).
+struct Resolved {
+  uint32_t t_key;
+  int64_t n_above, quota, count_t;
+  bool partial;                                     // the threshold code is only partly kept
+};
+
+template <class H>
+__device__ bool resolve_counts(const FusedUnit& F, int64_t n, int64_t kept, const H* h, Resolved& r,
+                               uint32_t* status) {
+  r = Resolved{kNoSelectKey, 0, 0, 0, false};
+  if (F.flags & kFusedNone) return true;
   const int64_t k = F.k;
   const int W = (int)(F.hi - F.lo + 1u);
   const uint32_t p1 = prov_key(F);
-  int64_t cum = (int64_t)F.kept;
-  if (!(F.flags & kFusedAll))
+  int64_t cum = kept;
+  if (!(F.flags & kFusedAll)) {
     for (int c = 0; c < W; ++c)
-      if (F.lo + (uint32_t)c >= p1) cum -= F.h[c];
-  if (F.flags & kFusedAll) {
-    F.t_key = 0;
-    F.n_above = cum;
-    F.quota = k - cum;
-    F.count_t = n - cum;
-    F.cutoff = n;
-    return true;
+      if (F.lo + (uint32_t)c >= p1) cum -= (int64_t)h[c];
+    if (k <= cum) return false;                     // threshold above the bracket
+    for (int c = W - 1; c >= 0; --c) {
+      const uint32_t code = F.lo + (uint32_t)c;
+      if (code == 0u) break;                        // zeros are not counted
+      const int64_t hc = (int64_t)h[c];
+      if (cum + hc >= k) {
+        r = Resolved{code, cum, k - cum, hc, k - cum != hc};
+        if (code >= 0x7F80u) flag_status(status, kStatusNonFinite);
+        return true;
+      }
+      cum += hc;
+    }
+    if (F.lo != 0u) return false;                   // threshold below the bracket
   }
-  if (k <= cum) {                                   // threshold above the bracket
+  r = Resolved{0u, cum, k - cum, n - cum, false};   // every nonzero key is kept; the rest are zeros
+  return true;
+}
+
+__device__ bool resolve_delta(FusedUnit& F, int64_t n, int* tflag, uint32_t* status) {
+  Resolved r;
+  if (!resolve_counts(F, n, (int64_t)F.kept, F.h, r, status)) {
     atomicOr(tflag, kFlagMiss);
     return false;
   }
-  for (int c = W - 1; c >= 0; --c) {
-    const uint32_t code = F.lo + (uint32_t)c;
-    if (code == 0u) break;                          // zeros are not counted
-    const int64_t h = F.h[c];
-    if (cum + h >= k) {
-      F.t_key = code;
-      F.n_above = cum;
-      F.quota = k - cum;
-      F.count_t = h;
-      F.cutoff = (F.quota == h) ? n : -1;           // -1: found from the records
-      if (code >= 0x7F80u) flag_status(status, kStatusNonFinite);
-      return true;
+  F.t_key = r.t_key;
+  F.n_above = r.n_above;
+  F.quota = r.quota;
+  F.count_t = r.count_t;
+  F.cutoff = (r.t_key == kNoSelectKey) ? 0 : r.partial ? -1 : n;   // -1: found from the records
+  return true;
+}
+
+// One workgroup per group: the members' counts added per delta, the group's threshold, then each
+// member's share of the threshold entries, in table order.  A flagged member or a missed bracket flags
+// every member (the thresholds are joint, so one tensor alone cannot be redone).
+__global__ void __launch_bounds__(1024) k_fs_group(const DevTensor* __restrict__ tab, int K, FusedGroups G,
+                                                   FusedUnit* __restrict__ fu, int* __restrict__ tflag,
+                                                   uint32_t* status) {
+  __shared__ int64_t sh[17];
+  __shared__ unsigned long long s_sum[32];          // kept, then the bracket codes
+  __shared__ int64_t s_h[kFusedMaxW];
+  __shared__ Resolved s_r;
+  __shared__ int s_bad;
+  const int g = blockIdx.x;
+  const int m0 = G.gmem0[g], m1 = G.gmem0[g + 1];
+  if (threadIdx.x == 0) s_bad = 0;
+  __syncthreads();
+  for (int m = m0 + threadIdx.x; m < m1; m += blockDim.x)
+    if (tflag[G.gmem[m]]) atomicOr(&s_bad, 1);
+  __syncthreads();
+  for (int i = 0; i < K; ++i) {
+    if (threadIdx.x < 32) s_sum[threadIdx.x] = 0ull;
+    __syncthreads();
+    const int c = threadIdx.x & 31;                 // 32 members at a time, one count per thread
+    if (c < kFusedStat) {
+      unsigned long long acc = 0;
+      for (int m = m0 + (threadIdx.x >> 5); m < m1; m += blockDim.x >> 5) {
+        const FusedUnit& F = fu[G.gmem[m] * K + i];
+        acc += (c == 0) ? (unsigned long long)F.kept : (unsigned long long)F.h[c - 1];
+      }
+      if (acc) atomicAdd(&s_sum[c], acc);
     }
-    cum += h;
+    __syncthreads();
+    const FusedUnit& F0 = fu[G.gmem[m0] * K + i];   // bracket, flags and k are every member's
+    if (threadIdx.x == 0 && !s_bad) {
+      for (int q = 0; q < kFusedMaxW; ++q) s_h[q] = (int64_t)s_sum[1 + q];
+      if (!resolve_counts(F0, G.gn[g], (int64_t)s_sum[0], s_h, s_r, status)) s_bad = 1;
+    }
+    __syncthreads();
+    if (s_bad) break;                               // the same for all threads
+    const uint32_t tk = s_r.t_key;
+    const int64_t quota = s_r.quota;
+    const bool codes = tk != kNoSelectKey && tk != 0u;
+    const int ct = codes ? (int)(tk - F0.lo) : 0;
+    int64_t before = 0;                             // threshold entries of earlier members
+    for (int mb = m0; mb < m1; mb += blockDim.x) {
+      const int m = mb + (int)threadIdx.x;
+      const int j = (m < m1) ? G.gmem[m] : -1;
+      const int64_t ties = (j >= 0 && codes) ? (int64_t)fu[j * K + i].h[ct] : 0;
+      const int64_t prev = before + block_scan(ties, sh) - ties;
+      if (j >= 0) {
+        FusedUnit& F = fu[j * K + i];
+        const int64_t take = max<int64_t>(0, min(ties, quota - prev));
+        F.t_key = tk;
+        F.quota = take;
+        F.count_t = ties;
+        F.cutoff = (tk == kNoSelectKey) ? 0 : (take == ties) ? tab[j].n : (take == 0) ? 0 : -1;
+      }
+      before += sh[16];
+    }
+    __syncthreads();                                // s_r is written again
   }
-  if (F.lo == 0u) {                                 // every nonzero key is kept; the rest are zeros
-    F.t_key = 0;
-    F.n_above = cum;
-    F.quota = k - cum;
-    F.count_t = n - cum;
-    F.cutoff = n;
-    return true;
-  }
-  atomicOr(tflag, kFlagMiss);                       // threshold below the bracket
-  return false;
+  if (s_bad)
+    for (int m = m0 + threadIdx.x; m < m1; m += blockDim.x) atomicOr(&tflag[G.gmem[m]], kFlagMiss);
 }
 
 struct TieArgs {
@@ -828,9 +968,10 @@ struct TieArgs {
   const uint32_t* rec;
   int64_t tile_cap;
   uint32_t* status;
+  const int* gid;            // null: no joint selection
 };
 
-// One workgroup per delta: its exact threshold, then, where the threshold code is only partly kept, the
+// One workgroup per delta: its exact threshold (a group's is resolved before), then, where the threshold code is only partly kept, the
 // reduction chunk, the tile and the record holding the quota-th entry of that code in flat order.
 // (Another delta's workgroup may flag the tensor meanwhile: what is found here is then not used.)
 template <int K>
@@ -843,7 +984,9 @@ __global__ void __launch_bounds__(1024) k_fs_tiefind(TieArgs a) {
   const DevTensor& T = a.tab[j];
   __shared__ int s_go;
   if (threadIdx.x == 0)
-    s_go = !a.tflag[j] && resolve_delta(a.fu[u], T.n, &a.tflag[j], a.status) && a.fu[u].cutoff < 0;
+    s_go = !a.tflag[j] &&
+           ((a.gid != nullptr && a.gid[j] >= 0) || resolve_delta(a.fu[u], T.n, &a.tflag[j], a.status)) &&
+           a.fu[u].cutoff < 0;
   __syncthreads();
   if (!s_go) return;
   const int64_t quota = a.fu[u].quota;
@@ -1121,12 +1264,13 @@ template <int K>
 hipError_t launch_k(const FusedPlan& pl, hipStream_t s) {
   const int nu = pl.n_t * K;
   const int parts = sample_parts(nu);
-  if (parts > 1) {
-    k_fs_init<<<(unsigned)(nu * (kBins / 4 / 256)), 256, 0, s>>>(pl.tab, pl.n_t, K, pl.fu, pl.tflag, pl.sel.hist);
-    k_fs_sample_part<<<dim3((unsigned)parts, (unsigned)nu), 1024, 0, s>>>(pl.tab, K, pl.fu, pl.sel.hist);
-    k_fs_bracket<<<nu, 1024, 0, s>>>(pl.tab, K, pl.fu, pl.tflag, pl.sel.hist);
+  if (parts > 1 || pl.grp.n_groups > 0) {
+    k_fs_init<<<(unsigned)(nu * (kBins / 4 / 256)), 256, 0, s>>>(pl.tab, pl.n_t, K, pl.fu, pl.tflag, pl.sel.hist,
+                                                                 pl.grp);
+    k_fs_sample_part<<<dim3((unsigned)nu, (unsigned)parts), 1024, 0, s>>>(pl.tab, K, pl.fu, pl.sel.hist, pl.grp);
+    k_fs_bracket<<<nu, 1024, 0, s>>>(pl.tab, K, pl.fu, pl.tflag, pl.sel.hist, pl.grp);
   } else {
-    k_fs_init<<<(std::max(nu, pl.n_t) + 255) / 256, 256, 0, s>>>(pl.tab, pl.n_t, K, pl.fu, pl.tflag, nullptr);
+    k_fs_init<<<(std::max(nu, pl.n_t) + 255) / 256, 256, 0, s>>>(pl.tab, pl.n_t, K, pl.fu, pl.tflag, nullptr, pl.grp);
     k_fs_sample<<<nu, 1024, 0, s>>>(pl.tab, K, pl.fu, pl.tflag);
   }
   if (pl.tiles > 0) {
@@ -1136,6 +1280,7 @@ hipError_t launch_k(const FusedPlan& pl, hipStream_t s) {
     m.n_t = pl.n_t;
     m.fu = pl.fu;
     m.tflag = pl.tflag;
+    m.early = pl.grp.n_groups > 0 ? pl.tflag : nullptr;
     m.tstat = pl.tstat;
     m.tinfo = pl.tinfo;
     m.rec = pl.rec;
@@ -1152,6 +1297,8 @@ hipError_t launch_k(const FusedPlan& pl, hipStream_t s) {
   if (pl.ritems > 0)
     k_fs_reduce<K><<<(unsigned)(pl.ritems / K), 1024, 0, s>>>(pl.tab, pl.n_t, pl.ritem0, pl.tflag, pl.tstat, pl.csum,
                                                                pl.fu);
+  if (pl.grp.n_groups > 0)
+    k_fs_group<<<(unsigned)pl.grp.n_groups, 1024, 0, s>>>(pl.tab, K, pl.grp, pl.fu, pl.tflag, pl.status);
   TieArgs ta;
   ta.tab = pl.tab;
   ta.fu = pl.fu;
@@ -1163,6 +1310,7 @@ hipError_t launch_k(const FusedPlan& pl, hipStream_t s) {
   ta.rec = pl.rec;
   ta.tile_cap = pl.tile_cap;
   ta.status = pl.status;
+  ta.gid = pl.grp.gid;
   k_fs_tiefind<K><<<nu, 1024, 0, s>>>(ta);
   if (pl.groups > 0) {
     FixArgs fa;
@@ -1194,6 +1342,8 @@ hipError_t launch_k(const FusedPlan& pl, hipStream_t s) {
 }  // namespace
 
 int64_t fused_tile_elems() { return kTileElems; }
+
+int64_t fused_sample_span() { return kSampleSpan; }
 
 int64_t fused_groups(int64_t n) {
   const int64_t nt = (n + kTileElems - 1) / kTileElems;

@@ -270,12 +270,14 @@ __global__ void __launch_bounds__(kHistThreads) k_hist_flagged(const DevTensor* 
 // selected), the flagged tensors' global histograms cleared, their number added to *flagged.
 __global__ void __launch_bounds__(1024) k_select_init_flagged(const DevTensor* __restrict__ tab, int n_t, int K,
                                                               UnitState* __restrict__ st, uint32_t* __restrict__ hist,
-                                                              const int* __restrict__ filter, uint32_t* flagged) {
+                                                              const int* __restrict__ filter, uint32_t* flagged,
+                                                              const int* gid, const int64_t* gk) {
   __shared__ int sflag[1024];
   for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < (int64_t)n_t * K; u += (int64_t)gridDim.x * blockDim.x) {
     const int j = (int)(u / K);
     const bool on = filter[j] != 0;
-    st[u] = unit_start(tab[j], tab[j].k, !on);
+    const int g = (gid != nullptr) ? gid[j] : -1;
+    st[u] = unit_start(tab[j], (g >= 0) ? gk[g] : tab[j].k, !on);
     if (on && u % K == 0 && flagged != nullptr) atomicAdd(flagged, 1u);
   }
   for_flagged_items(
@@ -384,10 +386,13 @@ __global__ void __launch_bounds__(kHistThreads) k_resolve(const DevTensor* __res
 // give its descriptor unchanged.
 
 // Group bins are 64-bit: a group (a whole-model delta) can hold more than 2^32 entries even
-// though each member's own counts fit 32 bits.
+// though each member's own counts fit 32 bits.  With a filter only flagged groups are selected (a
+// group's members are flagged together).
 __global__ void __launch_bounds__(256) k_group_sum(int K, const int* __restrict__ gmem, const int* __restrict__ gmem0,
-                                                   const uint32_t* __restrict__ hist, uint64_t* __restrict__ ghist) {
+                                                   const uint32_t* __restrict__ hist, uint64_t* __restrict__ ghist,
+                                                   const int* __restrict__ filter) {
   const int gi = blockIdx.y, g = gi / K, i = gi % K;
+  if (filter != nullptr && !filter[gmem[gmem0[g]]]) return;
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b >= kMaxBins) return;
   uint64_t sum = 0;
@@ -402,12 +407,13 @@ __global__ void __launch_bounds__(kHistThreads) k_group_resolve(const DevTensor*
                                                                 const int* __restrict__ gmem0,
                                                                 const int64_t* __restrict__ gk,
                                                                 const uint64_t* __restrict__ ghist,
-                                                                GroupState* __restrict__ gst, uint32_t* status) {
+                                                                GroupState* __restrict__ gst, uint32_t* status,
+                                                                const int* __restrict__ filter) {
   __shared__ int64_t sh[16];
   __shared__ int64_t found_d, found_above, total_nonzero;
   const int gi = blockIdx.x, g = gi / K;
   const int64_t need = gk[g];
-  if (need == 0) {
+  if (need == 0 || (filter != nullptr && !filter[gmem[gmem0[g]]])) {
     if (threadIdx.x == 0) gst[gi] = GroupState{kNoSelectKey, 1, 0};
     return;
   }
@@ -872,13 +878,14 @@ static hipError_t run_select_t(const SelectPlan& pl, hipStream_t s) {
   const int nu = pl.n_t * pl.K;
   const bool flt = pl.filter != nullptr;
   constexpr unsigned kFlaggedGrid = 256;
-  // the entry points reject groups of fp32 tensors, and groups do not take the single-read path
-  if (pl.n_groups > 0 && (DT != ISO_BF16 || flt)) return hipErrorInvalidValue;
+  // the entry points reject groups of fp32 tensors
+  if (pl.n_groups > 0 && DT != ISO_BF16) return hipErrorInvalidValue;
+  const int* gid = pl.n_groups > 0 ? pl.gid : nullptr;
   if (flt)
-    k_select_init_flagged<<<kFlaggedGrid, 1024, 0, s>>>(pl.tab, pl.n_t, pl.K, pl.states, pl.hist, pl.filter, pl.flagged);
+    k_select_init_flagged<<<kFlaggedGrid, 1024, 0, s>>>(pl.tab, pl.n_t, pl.K, pl.states, pl.hist, pl.filter, pl.flagged,
+                                                        gid, pl.gk);
   else
-    k_select_init<<<(nu + 255) / 256, 256, 0, s>>>(pl.tab, pl.n_t, pl.K, pl.states, pl.n_groups > 0 ? pl.gid : nullptr,
-                                                   pl.gk);
+    k_select_init<<<(nu + 255) / 256, 256, 0, s>>>(pl.tab, pl.n_t, pl.K, pl.states, gid, pl.gk);
   struct Pass { int shift, bits; };
   const Pass bf[1] = {{0, 15}};
   const Pass f32[3] = {{16, 15}, {8, 8}, {0, 8}};
@@ -896,9 +903,10 @@ static hipError_t run_select_t(const SelectPlan& pl, hipStream_t s) {
                                                                   q == 0, pl.status, dump);
     if (pl.n_groups > 0) {
       const int ngk = pl.n_groups * pl.K;
-      k_group_sum<<<dim3(kMaxBins / 256, (unsigned)ngk), 256, 0, s>>>(pl.K, pl.gmem, pl.gmem0, pl.hist, pl.ghist);
+      k_group_sum<<<dim3(kMaxBins / 256, (unsigned)ngk), 256, 0, s>>>(pl.K, pl.gmem, pl.gmem0, pl.hist, pl.ghist,
+                                                                    pl.filter);
       k_group_resolve<<<ngk, kHistThreads, 0, s>>>(pl.tab, pl.K, pl.gmem, pl.gmem0, pl.gk, pl.ghist, pl.gstate,
-                                                   pl.status);
+                                                   pl.status, pl.filter);
       k_member_counts<<<nu, 1024, 0, s>>>(pl.tab, pl.K, pl.gid, pl.gstate, pl.hist, pl.mcnt);
       k_group_assign<<<(ngk + 63) / 64, 64, 0, s>>>(pl.n_groups, pl.K, pl.gmem, pl.gmem0, pl.gstate, pl.mcnt,
                                                     pl.states);

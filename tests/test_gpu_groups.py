@@ -139,3 +139,96 @@ def test_whole_layer_as_one_group():
     u = units[-1]
     ref = ties.merge_unit(u.base, u.deltas, "bf16", "ties", masks=masks_last)["out"]
     assert np.array_equal(from_dev(u.dout, u.n, "bf16"), ref)
+
+
+def _flat_group_call(case, seed=5):
+    """Table of a case: entries over flat device buffers, their base / out / sign buffers."""
+    import torch
+    shapes, K = case["shapes"], case["K"]
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    offs, at = [], 0
+    for r, c, _, _ in shapes:
+        offs.append(at)
+        at += -(-r * c // 16) * 16
+    base = torch.randn(max(at, 16), generator=g, device="cuda").mul_(0.02).to(torch.bfloat16)
+    ds = [case["fill"](max(at, 16), g).to(torch.bfloat16) for _ in range(K)]
+    out, sign = torch.zeros_like(base), torch.zeros(base.numel(), dtype=torch.int8, device="cuda")
+    cut = lambda x: [x[o:o + max(1, r * c)] for o, (r, c, _, _) in zip(offs, shapes)]   # an empty tensor's address is valid
+    parts = [cut(x) for x in [base, out] + ds]
+    es = [iso.Entry(r, c, base=parts[0][j], out=parts[1][j], deltas=[p[j] for p in parts[2:]], k=k, group=grp)
+          for j, (r, c, grp, k) in enumerate(shapes)]
+    return es, base, out, sign, cut(sign)
+
+
+def _randn(scale):
+    import torch
+    return lambda n, g: torch.randn(n, generator=g, device="cuda").mul_(scale)
+
+
+def _few_magnitudes(n, g):
+    import torch
+    m = torch.tensor([0.0, 1e-4, 2e-4, 5e-4, 1e-3], device="cuda")
+    p = torch.tensor([0.4, 0.3, 0.15, 0.1, 0.05], device="cuda")
+    x = m[torch.bucketize(torch.rand(n, generator=g, device="cuda"), p.cumsum(0)[:-1])]
+    return x * (torch.randint(0, 2, (n,), generator=g, device="cuda") * 2 - 1)
+
+
+def _odd_blocks_large(n, g):
+    """256-entry blocks of large and small magnitudes in turn: a sample of every second block misleads."""
+    import torch
+    x = torch.randn(n, generator=g, device="cuda") * 1e-4
+    return x * (1 + 15 * ((torch.arange(n, device="cuda") // 256) % 2))
+
+
+BIG = (8192, 8192)                                   # 2^26 entries, from which the single read is taken: 2^18 blocks,
+ALONE = (*BIG, 0, 3000000)                           # of which 2^12 are sampled; alone, or as a member
+JOINT = dict(
+    ragged=dict(K=4, fill=_randn(1e-4), shapes=[(1537, 2053, 1, 300000), (0, 7, 1, 0), ALONE, (13, 17, 2, 30), (1, 255, 1, 99),
+                                                (700, 1999, 2, 90000), (511, 1025, 0, 20000), (1001, 1003, 1, 0)]),
+    many_members=dict(K=3, fill=_randn(1e-4), shapes=[(3, 5 + j % 91, 1 + (j % 7 == 0), j % 5) for j in range(1300)] +
+                      [(1 << 11, 1 << 9, 1, 200000), ALONE]),
+    ties_full_records=dict(K=2, fill=_few_magnitudes, shapes=[(1025, 1031, 3, 400000), (999, 777, 3, 0), (640, 4096, 3, 77),
+                                                              ALONE]),
+    missed_bracket=dict(K=2, fill=_odd_blocks_large, shapes=[(*BIG, 1, 200000), (1024, 4096, 2, 300000)]),
+    all_kept=dict(K=2, fill=_randn(1e-3), shapes=[(*BIG, 1, 8192 * 8192 + 999), (27, 37, 1, 0), (1024, 1024, 2, 0)]),
+    eight_experts=dict(K=8, fill=_randn(5e-5), shapes=[(*BIG, 1, 10000000), (900, 901, 1, 90000), (1000, 1100, 1, 1)]),
+    zeros_kept=dict(K=2, fill=lambda n, g: _randn(1e-4)(n, g) * (_randn(1.0)(n, g) > 1.0),
+                    shapes=[(*BIG, 1, 50000000), (500, 777, 1, 300000)]),
+)
+
+
+@pytest.mark.parametrize("lam,want_sign", [(1.0, False), (0.3, True)])
+@pytest.mark.parametrize("name", list(JOINT))
+def test_joint_single_read_equals_two_passes(name, lam, want_sign):
+    """The joint selection inside one call against the same selection as a call of its own (its descriptors
+    are checked against the oracle above) followed by the two-pass merge: equal bytes, on new buffers, in
+    a workspace that holds two passes only, and with the weights written over the base."""
+    import torch
+    case = JOINT[name]
+    K = case["K"]
+    es, base, out, sign, views = _flat_group_call(case)
+    say(f"joint {name}: {len(es)} tensors, K = {K}, lambda = {lam}, sign {want_sign}")
+    kw = dict(merge=iso.MERGE_TIES, lam=lam, sign_out=views if want_sign else None)
+    desc = iso.desc_tensor(len(es) * K)
+    wst = iso.workspace(iso.OP_TOPK, es, K, iso.BF16)
+    iso.iso_topk_mask(es, K, iso.BF16, desc, ws=wst)
+    wsd = iso.workspace(iso.OP_UPDATE_FUSED, es, K, iso.BF16)
+    iso.iso_update(es, K, iso.BF16, iso.UPDATE_FUSED, desc=desc, ws=wsd, **kw)
+    want, want_s = out.clone(), sign.clone()
+    ws = iso.workspace(iso.OP_UPDATE_FUSED_SELECT, es, K, iso.BF16)
+    for what, w in (("own workspace", ws), ("again", ws), ("two-pass workspace", wst)):
+        out.zero_()
+        sign.zero_()
+        iso.iso_update(es, K, iso.BF16, iso.UPDATE_FUSED, desc=None, ws=w, **kw)
+        assert iso.iso_read_device_status(w) == 0, what
+        if w is ws:
+            say(f"joint {name}, {what}: {iso.iso_read_fallback_count(ws)} tensors by two passes")
+        assert torch.equal(out.view(torch.int16), want.view(torch.int16)), what
+        assert torch.equal(sign, want_s), what
+    for e in es:
+        e.out = e.base
+    iso.iso_update(es, K, iso.BF16, iso.UPDATE_FUSED, desc=None, ws=ws, **kw)
+    at = 0
+    for r, c, _, _ in case["shapes"]:
+        assert torch.equal(base[at:at + r * c].view(torch.int16), want[at:at + r * c].view(torch.int16)), "in place"
+        at += -(-r * c // 16) * 16
