@@ -396,12 +396,17 @@ __global__ void __launch_bounds__(256) k_group_sum(int K, const int* __restrict_
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b >= kMaxBins) return;
   uint64_t sum = 0;
-  for (int m = gmem0[g]; m < gmem0[g + 1]; ++m) sum += hist[((size_t)gmem[m] * K + i) * kMaxBins + b];
+  const int m1 = gmem0[g + 1];
+#pragma unroll 8
+  for (int m = gmem0[g]; m < m1; ++m) sum += hist[((size_t)gmem[m] * K + i) * kMaxBins + b];
   ghist[(size_t)gi * kMaxBins + b] = sum;
 }
 
-// The group histogram (256 KB of 64-bit bins) does not fit LDS: each thread reads its run of
-// consecutive bins from global memory twice (sum, then the walk from the top).
+// The group histogram (256 KB of 64-bit bins) does not fit LDS; one workgroup reads it once, 32 bins a
+// thread, kept in registers: a wave holds 2048 consecutive bins, read as 32 whole lines of 64.  The wave
+// the rank falls into sums its lines from the top, eight at a time, and scans the line it ends in.
+// Bound by the latency of that chain.  (Each thread reading a run of 32
+// bins, twice: 35 us against 16 us.)
 __global__ void __launch_bounds__(kHistThreads) k_group_resolve(const DevTensor* __restrict__ tab, int K,
                                                                 const int* __restrict__ gmem,
                                                                 const int* __restrict__ gmem0,
@@ -409,41 +414,73 @@ __global__ void __launch_bounds__(kHistThreads) k_group_resolve(const DevTensor*
                                                                 const uint64_t* __restrict__ ghist,
                                                                 GroupState* __restrict__ gst, uint32_t* status,
                                                                 const int* __restrict__ filter) {
-  __shared__ int64_t sh[16];
-  __shared__ int64_t found_d, found_above, total_nonzero;
+  constexpr int kLines = kMaxBins / kHistThreads, kWaves = kHistThreads / 64, kStep = 8;
+  __shared__ int64_t sh[kWaves];
+  __shared__ int64_t found_d, found_above;
   const int gi = blockIdx.x, g = gi / K;
   const int64_t need = gk[g];
   if (need == 0 || (filter != nullptr && !filter[gmem[gmem0[g]]])) {
     if (threadIdx.x == 0) gst[gi] = GroupState{kNoSelectKey, 1, 0};
     return;
   }
-  int64_t n_g = 0;
-  for (int m = gmem0[g]; m < gmem0[g + 1]; ++m) n_g += tab[gmem[m]].n;
-  const uint64_t* gh = ghist + (size_t)gi * kMaxBins;
-  if (threadIdx.x == 0) { found_d = -1; found_above = 0; }
-  __syncthreads();
-  const uint32_t per = (kMaxBins + blockDim.x - 1) / blockDim.x;
-  const uint32_t b0 = threadIdx.x * per;
-  int64_t mine = 0;
-  for (uint32_t q = 0; q < per; ++q) {
-    const uint32_t b = b0 + q;
-    if (b < kMaxBins && b > 0) mine += (int64_t)gh[b];
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const uint64_t* gh = ghist + (size_t)gi * kMaxBins + wid * (64 * kLines) + lane;
+  int64_t v[kLines], mine = 0;
+#pragma unroll
+  for (int q = 0; q < kLines; ++q) v[q] = (int64_t)gh[q * 64];
+  if (threadIdx.x == 0) {
+    v[0] = 0;                                       // bin 0 is not counted: the zeros are what is left
+    found_d = -1;
+    found_above = 0;
   }
-  const int64_t incl = block_inclusive_scan(mine, sh);
-  if (threadIdx.x == blockDim.x - 1) total_nonzero = incl;
+#pragma unroll
+  for (int q = 0; q < kLines; ++q) mine += v[q];
+  for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o, 64);
+  if (lane == 0) sh[wid] = mine;
   __syncthreads();
-  const int64_t zeros = n_g - total_nonzero;
-  int64_t run = total_nonzero - incl;
-  for (int q = (int)per - 1; q >= 0; --q) {
-    const uint32_t b = b0 + (uint32_t)q;
-    if (b >= kMaxBins) continue;
-    const int64_t h = (b == 0) ? zeros : (int64_t)gh[b];
-    if (run < need && run + h >= need) { found_d = b; found_above = run; }
-    run += h;
+  int64_t run = 0, total = 0;                       // entries above this wave's bins; all nonzero entries
+  for (int w = 0; w < kWaves; ++w) {
+    total += sh[w];
+    if (w > wid) run += sh[w];
+  }
+  if (run < need && run + mine >= need) {           // the same for the whole wave
+    bool done = false;
+#pragma unroll
+    for (int q0 = kLines - kStep; q0 >= 0; q0 -= kStep) {
+      int64_t line[kStep];
+#pragma unroll
+      for (int e = 0; e < kStep; ++e) line[e] = v[q0 + e];
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+        for (int e = 0; e < kStep; ++e) line[e] += __shfl_xor(line[e], o, 64);
+#pragma unroll
+      for (int e = kStep - 1; e >= 0; --e) {
+        if (!done && run + line[e] >= need) {
+          int64_t suf = v[q0 + e];                  // entries of this line's bins from the lane's on
+          for (int o = 1; o < 64; o <<= 1) {
+            const int64_t y = __shfl_down(suf, o, 64);
+            if (lane + o < 64) suf += y;
+          }
+          const int64_t above = run + suf - v[q0 + e];
+          if (above < need && run + suf >= need) {
+            found_d = wid * (64 * kLines) + (q0 + e) * 64 + lane;
+            found_above = above;
+          }
+          done = true;
+        }
+        run += line[e];
+      }
+    }
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    if (found_d < 0) flag_status(status, kStatusInternal);
+    if (found_d < 0) {                              // every nonzero entry is kept, and some of the zeros
+      int64_t n_g = 0;
+      for (int m = gmem0[g]; m < gmem0[g + 1]; ++m) n_g += tab[gmem[m]].n;
+      if (n_g < need) flag_status(status, kStatusInternal);
+      found_above = total;
+    }
     gst[gi] = GroupState{(uint32_t)(found_d < 0 ? 0 : found_d), 0, need - found_above};
   }
 }
@@ -460,11 +497,19 @@ __global__ void __launch_bounds__(1024) k_member_counts(const DevTensor* __restr
   const GroupState G = gst[g * K + i];
   if (G.none) return;
   const uint32_t* h = hist + (size_t)u * kMaxBins;
+  constexpr int kVecs = kMaxBins / 4 / 1024;
+  uint4 x[kVecs];
+#pragma unroll
+  for (int q = 0; q < kVecs; ++q) x[q] = ((const uint4*)h)[q * 1024 + threadIdx.x];
   int64_t above = 0, nonzero = 0;
-  for (uint32_t b = threadIdx.x + 1; b < kMaxBins; b += blockDim.x) {
-    const int64_t v = h[b];
-    nonzero += v;
-    if (b > G.t_key) above += v;
+#pragma unroll
+  for (int q = 0; q < kVecs; ++q) {
+    const uint32_t b = 4u * (uint32_t)(q * 1024 + threadIdx.x), w[4] = {x[q].x, x[q].y, x[q].z, x[q].w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (b + e > 0u) nonzero += w[e];
+      if (b + e > G.t_key) above += w[e];
+    }
   }
   above = block_inclusive_scan(above, sh);
   __syncthreads();
@@ -475,28 +520,36 @@ __global__ void __launch_bounds__(1024) k_member_counts(const DevTensor* __restr
   }
 }
 
-// One thread per (group, delta): the threshold entries go to the members in table order.
-__global__ void k_group_assign(int n_groups, int K, const int* __restrict__ gmem, const int* __restrict__ gmem0,
-                               const GroupState* __restrict__ gst, const int64_t* __restrict__ mcnt,
-                               UnitState* __restrict__ st) {
-  const int gi = blockIdx.x * blockDim.x + threadIdx.x;
-  if (gi >= n_groups * K) return;
-  const int g = gi / K, i = gi % K;
+// One workgroup per (group, delta): the threshold entries go to the members in table order, 256
+// members at a time (one thread walking 56 members took 23 us, a chain of dependent loads).
+__global__ void __launch_bounds__(256) k_group_assign(int K, const int* __restrict__ gmem,
+                                                      const int* __restrict__ gmem0,
+                                                      const GroupState* __restrict__ gst,
+                                                      const int64_t* __restrict__ mcnt, UnitState* __restrict__ st) {
+  __shared__ int64_t sh[16];
+  __shared__ int64_t s_total;
+  const int gi = blockIdx.x, g = gi / K, i = gi % K;
   const GroupState G = gst[gi];
   if (G.none) return;
-  int64_t rem = G.quota;
-  for (int m = gmem0[g]; m < gmem0[g + 1]; ++m) {
-    const int u = gmem[m] * K + i;
-    if (st[u].done) continue;                       // an empty member
-    const int64_t ties = mcnt[2 * (size_t)u + 1];
-    const int64_t take = rem < ties ? rem : ties;
-    rem -= take;
-    const int64_t kk = mcnt[2 * (size_t)u] + take;
-    st[u].k_rem = kk;
-    if (kk == 0) {
-      st[u].done = 1;
-      st[u].prefix = kNoSelectKey;
+  int64_t before = 0;                               // threshold entries of earlier members
+  for (int mb = gmem0[g]; mb < gmem0[g + 1]; mb += blockDim.x) {
+    const int m = mb + (int)threadIdx.x;
+    const int u = (m < gmem0[g + 1]) ? gmem[m] * K + i : -1;
+    const bool on = u >= 0 && !st[u].done;          // an empty member is done
+    const int64_t ties = on ? mcnt[2 * (size_t)u + 1] : 0;
+    const int64_t incl = before + block_inclusive_scan(ties, sh);
+    if (threadIdx.x == blockDim.x - 1) s_total = incl;
+    if (on) {
+      const int64_t kk = mcnt[2 * (size_t)u] + max<int64_t>(0, min(ties, G.quota - (incl - ties)));
+      st[u].k_rem = kk;
+      if (kk == 0) {
+        st[u].done = 1;
+        st[u].prefix = kNoSelectKey;
+      }
     }
+    __syncthreads();
+    before = s_total;
+    __syncthreads();
   }
 }
 
@@ -908,8 +961,7 @@ static hipError_t run_select_t(const SelectPlan& pl, hipStream_t s) {
       k_group_resolve<<<ngk, kHistThreads, 0, s>>>(pl.tab, pl.K, pl.gmem, pl.gmem0, pl.gk, pl.ghist, pl.gstate,
                                                    pl.status, pl.filter);
       k_member_counts<<<nu, 1024, 0, s>>>(pl.tab, pl.K, pl.gid, pl.gstate, pl.hist, pl.mcnt);
-      k_group_assign<<<(ngk + 63) / 64, 64, 0, s>>>(pl.n_groups, pl.K, pl.gmem, pl.gmem0, pl.gstate, pl.mcnt,
-                                                    pl.states);
+      k_group_assign<<<ngk, 256, 0, s>>>(pl.K, pl.gmem, pl.gmem0, pl.gstate, pl.mcnt, pl.states);
     }
     if (q == np - 1 && pl.chunk_hist != nullptr)
       k_resolve_last<DT><<<nu, kHistThreads, 0, s>>>(pl.tab, pl.K, pl.hist_item0, pl.hist_chunk, pl.states, pl.hist,
