@@ -211,26 +211,27 @@ __device__ __forceinline__ int find_tensor_mapped(const DevTensor* tab, const in
 
 // Persistent-grid walk over the work of flagged tensors only.  Every block scans the flags
 // (through LDS, 1024 at a time) in tensor order and takes every gridDim.x-th work item of
-// the flagged tensors; count(j) gives tensor j's item count.  With no flag set a block
+// the flagged tensors; count(j) gives tensor j's item count (below 2^31), taken by a thread per
+// tensor: a walk that read each tensor's size in turn took 0.3 us a tensor.  With no flag set a block
 // only reads the flags.  body(j, item) may synchronise the block: the loop is uniform.
 template <class Count, class Body>
 __device__ __forceinline__ void for_flagged_items(const int* __restrict__ flags, int n_t, int* sflag, Count count,
                                                   Body body) {
-  const int64_t G = gridDim.x;
-  int64_t run = 0;   // items of flagged tensors before tensor j
+  const uint32_t G = gridDim.x;
+  uint32_t run = 0;   // items of flagged tensors before tensor j, modulo G
   for (int j0 = 0; j0 < n_t; j0 += 1024) {
     __syncthreads();
-    for (int q = threadIdx.x; q < 1024; q += blockDim.x) sflag[q] = (j0 + q < n_t) ? flags[j0 + q] : 0;
+    for (int q = threadIdx.x; q < 1024; q += blockDim.x)
+      sflag[q] = (j0 + q < n_t && flags[j0 + q]) ? (int)count(j0 + q) : 0;
     __syncthreads();
     const int nq = min(1024, n_t - j0);
     for (int q = 0; q < nq; ++q) {
-      if (!sflag[q]) continue;
+      const int64_t m = sflag[q];
+      if (m == 0) continue;
       const int j = j0 + q;
-      const int64_t m = count(j);
-      int64_t first = ((int64_t)blockIdx.x - run) % G;
-      if (first < 0) first += G;
+      const uint32_t first = (blockIdx.x >= run) ? blockIdx.x - run : blockIdx.x + G - run;
       for (int64_t it = first; it < m; it += G) body(j, it);
-      run += m;
+      run = (run + (uint32_t)m) % G;
     }
   }
 }
