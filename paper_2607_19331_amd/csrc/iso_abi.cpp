@@ -147,7 +147,7 @@ bool fused_eligible(int op, int n_t, int dt) {
 // less below (K = 8: 2^21 coordinates 120 against 175 us, 2^24 240 against 240); at 2^26 one read
 // takes K = 1: 144 against 185 us, K = 2: 179 / 234, K = 4: 260 / 349, K = 8: 457 / 568, at 2^27 four
 // deltas 393 against 576.  A group of few distinct magnitudes is given up after its sample and then
-// costs 80 to 200 us more than two passes alone, which the line keeps a small share.
+// costs 70 to 170 us more than two passes alone, which the line keeps a small share.
 constexpr int64_t kFusedGroupMin = 1ll << 26;
 
 // Whether a merged weight may be written over an input of its tensor.  The two-pass merge reads an

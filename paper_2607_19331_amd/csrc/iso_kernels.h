@@ -69,6 +69,9 @@ struct MergePlan {
   int64_t tiles;                // total tiles over the table
   uint32_t* status;
   const int* filter = nullptr;  // n_t device flags: only flagged tensors are merged; null: every tensor
+  // Workgroups with a filter.  4096 instead of 1024 merge a flagged group of 2^27 coordinates (two deltas, one
+  // member) in 562 instead of 595 us a call, and cost a call that flags nothing 2 us.
+  unsigned flagged_grid = 1024;
   hipEvent_t prof[2] = {nullptr, nullptr};   // recorded around the merge kernel when set
 };
 

@@ -339,8 +339,8 @@ __global__ void __launch_bounds__(kMergeThreads) k_apply(const DevTensor* __rest
 template <int DT, int K, int MODE, int OUTS>
 static void launch_merge(const MergePlan& pl, hipStream_t s) {
   if (pl.filter != nullptr) {
-    k_merge_flagged<DT, K, MODE, OUTS, kMergeVPT><<<1024, kMergeThreads, 0, s>>>(pl.tab, pl.n_t, pl.desc, pl.lambda,
-                                                                                 pl.eps, pl.status, pl.filter);
+    k_merge_flagged<DT, K, MODE, OUTS, kMergeVPT><<<pl.flagged_grid, kMergeThreads, 0, s>>>(
+        pl.tab, pl.n_t, pl.desc, pl.lambda, pl.eps, pl.status, pl.filter);
     return;
   }
   const int64_t grid = (kMergeMaxGrid > 0) ? std::min(pl.tiles, kMergeMaxGrid) : pl.tiles;
