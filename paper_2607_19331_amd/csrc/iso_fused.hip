@@ -44,6 +44,7 @@ constexpr double kMarginSd = 5.0;
 constexpr int kBins = 1 << 15;
 
 constexpr int kFlagWide = 1, kFlagFull = 2, kFlagMiss = 4;   // reasons, OR-ed into tflag
+constexpr int kFlagSample = 8;   // given up by the sample: set before the main pass and never by it
 
 __device__ __forceinline__ uint32_t bkey(uint32_t b) { return b & 0x7FFFu; }
 
@@ -268,7 +269,7 @@ __device__ void bracket_from(FusedUnit& F, int* tflag, const uint32_t* bins, int
     F.lo = lo;
     F.hi = max(hi, lo);
     F.prov = max(lo, min(F.hi, est));
-    if (F.hi - lo + 1u > (uint32_t)kFusedMaxW) atomicOr(tflag, kFlagWide);
+    if (F.hi - lo + 1u > (uint32_t)kFusedMaxW) atomicOr(tflag, kFlagWide | kFlagSample);
   }
 }
 
@@ -348,7 +349,7 @@ __global__ void __launch_bounds__(1024) k_fs_bracket(const DevTensor* __restrict
     F.lo = lo;
     F.hi = hi;
     F.prov = prov;
-    if (reason) atomicOr(&tflag[G.gmem[m]], reason);
+    if (reason) atomicOr(&tflag[G.gmem[m]], reason | kFlagSample);
   }
 }
 
@@ -495,7 +496,7 @@ struct MainArgs {
   int n_t;
   const FusedUnit* fu;
   int* tflag;
-  const int* early;        // tflag where the call has joint selections, else null
+  const int* early;        // tflag where the call has joint selections, else null (read for kFlagSample only)
   uint16_t* tstat;
   uint32_t one2;           // 0x00010001, passed in so that min(d, 1) stays one packed min
   uint2* tinfo;
@@ -524,7 +525,9 @@ k_fs_main(MainArgs a) {
   __shared__ int s_skip, s_redo;
   const int64_t tile = blockIdx.x;
   const int j = find_tensor_mapped(a.tab, a.tmap, a.n_t, tile);
-  if (a.early != nullptr && a.early[j]) return;     // uniform; a group given up by its sample is not read
+  // A group given up by its sample is not read.  Other workgroups of this launch set other bits of the word
+  // (kFlagFull), so only the bit that none of them writes is the same for every wave of this one.
+  if (a.early != nullptr && (a.early[j] & kFlagSample)) return;
   const DevTensor& T = a.tab[j];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   // the stream loads first: nothing below delays their issue
