@@ -98,7 +98,9 @@ __device__ __forceinline__ int sample_slot(const FusedGroups& G, int j) {
   return (g < 0) ? j : G.gmem[G.gmem0[g]];
 }
 
-// hist: the units' sample histograms, cleared when the sample is split (else null).
+// hist: the units' sample histograms, cleared when the sample is split (else null).  32-bit thread numbers:
+// a call may hold kFusedMaxTensors * ISO_MAX_K units, and one thread per 16 bytes of their histograms would
+// number past 2^31, so the clear strides over a bounded grid.
 __global__ void k_fs_init(const DevTensor* __restrict__ tab, int n_t, int K, FusedUnit* __restrict__ fu,
                           int* __restrict__ tflag, uint32_t* __restrict__ hist, FusedGroups G) {
   const int u = blockIdx.x * blockDim.x + threadIdx.x;
@@ -351,6 +353,14 @@ __global__ void __launch_bounds__(1024) k_fs_bracket(const DevTensor* __restrict
     F.prov = prov;
     if (reason) atomicOr(&tflag[G.gmem[m]], reason | kFlagSample);
   }
+}
+
+// Workgroups of k_fs_init with histograms to clear: a thread per unit at least, and no more than 4096 (16 per CU).
+constexpr int64_t kInitMaxBlocks = 4096;
+static_assert(kInitMaxBlocks * 256 >= (int64_t)kFusedMaxTensors * ISO_MAX_K, "a thread per unit");
+static_assert(kInitMaxBlocks * 256 <= INT32_MAX, "32-bit thread numbers");
+inline unsigned init_blocks(int nu) {
+  return (unsigned)std::min<int64_t>((int64_t)nu * (kBins / 4 / 256), kInitMaxBlocks);
 }
 
 // Workgroups per delta for the sample.  Each costs about as much as 2^17 entries besides its share
@@ -1268,8 +1278,7 @@ hipError_t launch_k(const FusedPlan& pl, hipStream_t s) {
   const int nu = pl.n_t * K;
   const int parts = sample_parts(nu);
   if (parts > 1 || pl.grp.n_groups > 0) {
-    k_fs_init<<<(unsigned)(nu * (kBins / 4 / 256)), 256, 0, s>>>(pl.tab, pl.n_t, K, pl.fu, pl.tflag, pl.sel.hist,
-                                                                 pl.grp);
+    k_fs_init<<<init_blocks(nu), 256, 0, s>>>(pl.tab, pl.n_t, K, pl.fu, pl.tflag, pl.sel.hist, pl.grp);
     k_fs_sample_part<<<dim3((unsigned)nu, (unsigned)parts), 1024, 0, s>>>(pl.tab, K, pl.fu, pl.sel.hist, pl.grp);
     k_fs_bracket<<<nu, 1024, 0, s>>>(pl.tab, K, pl.fu, pl.tflag, pl.sel.hist, pl.grp);
   } else {

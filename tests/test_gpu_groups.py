@@ -246,3 +246,26 @@ def test_joint_single_read_equals_two_passes(name, lam, want_sign):
     for r, c, _, _ in case["shapes"]:
         assert torch.equal(base[at:at + r * c].view(torch.int16), want[at:at + r * c].view(torch.int16)), "in place"
         at += -(-r * c // 16) * 16
+
+
+def test_joint_single_read_of_many_units():
+    """32769 tensors and K = 8: 262152 units, the first count at which a thread per 16 bytes of their histograms
+    would be numbered past 2^31.  The single read against the selection and merge as two calls."""
+    import torch
+    K, n = 8, 2048
+    case = dict(K=K, fill=_randn(1e-4), shapes=[(1, n, 1, n // 10)] * 32769)
+    es, base, out, _, _ = _flat_group_call(case)
+    say(f"joint, {len(es) * K} units")
+    desc = iso.desc_tensor(len(es) * K)
+    ws = iso.workspace(iso.OP_TOPK, es, K, iso.BF16)
+    iso.iso_topk_mask(es, K, iso.BF16, desc, ws=ws)
+    two_pass = ws.numel()
+    ws = iso.workspace(iso.OP_UPDATE_FUSED, es, K, iso.BF16)
+    iso.iso_update(es, K, iso.BF16, iso.UPDATE_FUSED, merge=iso.MERGE_TIES, desc=desc, ws=ws)
+    want = out.clone()
+    out.zero_()
+    ws = iso.workspace(iso.OP_UPDATE_FUSED_SELECT, es, K, iso.BF16)
+    assert ws.numel() > two_pass
+    iso.iso_update(es, K, iso.BF16, iso.UPDATE_FUSED, merge=iso.MERGE_TIES, desc=None, ws=ws)
+    assert iso.iso_read_device_status(ws) == 0 and iso.iso_read_fallback_count(ws) == 0
+    assert torch.equal(out.view(torch.int16), want.view(torch.int16))
