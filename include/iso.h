@@ -225,9 +225,11 @@ typedef struct iso_update_args {
  *            once the exact threshold is known.  A tensor whose threshold the
  *            bracket misses takes the two-pass path on the device; the result
  *            is the same (iso_read_fallback_count reports how many did); a
- *            group goes as one.  Calls with groups take the two-pass path below
- *            2^26 coordinates, where an output overlaps an input of its tensor,
- *            and in a workspace of ISO_OP_TOPK's size for the table.
+ *            group goes as one.  A call whose weights go over an input of
+ *            their tensor (out == base, or a delta) takes the two-pass path, as
+ *            do calls with groups below 2^26 coordinates and in a workspace of
+ *            ISO_OP_TOPK's size for the table.  (An output must not overlap its
+ *            tensor's inputs at another offset, nor another tensor's.)
  *  SPECTRAL: ISO-Merger, Sec. 4.2 / App. E / Algorithm 1, per matrix, in
  *            binary64: SVDs of W_0 and W_i = W_0 + tau_i, joint sign
  *            canonicalisation, tangent projection, D_keep, effect proxies and

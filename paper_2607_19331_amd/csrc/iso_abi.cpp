@@ -584,7 +584,10 @@ iso_status update_call(const iso_tensor* t, int n_t, int K, int dt, const iso_up
     if (want_sign && (st = check_ptr_array((const void* const*)a->sign_out, n_t, true)) != ISO_OK) return st;
     const bool inner_select = ties && a->desc == nullptr;
     const int op = inner_select ? ISO_OP_UPDATE_FUSED_SELECT : ISO_OP_UPDATE_FUSED;
-    Layout L = plan(op, t, n_t, K, dt, inner_select && !writes_inputs(t, n_t, K, dt));
+    // Two passes where an output overlaps an input.  Without joint selections they run in the single read's
+    // layout, which holds their regions, so that the call needs the same workspace either way.
+    const bool overlap = inner_select && writes_inputs(t, n_t, K, dt);
+    Layout L = plan(op, t, n_t, K, dt, !overlap);
     st = take_ws(src, L, &w);
     if (st != ISO_OK && L.fused && L.n_groups > 0) {   // joint selections in a workspace for two passes only
       L = plan(op, t, n_t, K, dt, false);
@@ -604,7 +607,7 @@ iso_status update_call(const iso_tensor* t, int n_t, int K, int dt, const iso_up
     mp.eps = a->eps_act;
     mp.tiles = L.tiles;
     mp.status = (uint32_t*)w;
-    if (L.fused) {
+    if (L.fused && !overlap) {
       iso_select_desc* dd = (iso_select_desc*)(w + L.desc);
       FusedPlan fp;
       fp.tab = mp.tab;

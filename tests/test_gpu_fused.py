@@ -208,3 +208,26 @@ def test_cancelling_base_takes_the_exact_rounding():
         outs, sg, st, fb = fused([u], K, lam=lam, want_sign=False)
         assert st == 0 and fb == 0
         assert np.array_equal(outs[0], ref["out"])
+
+
+@pytest.mark.parametrize("over", ["base", "delta"])
+def test_weights_written_over_an_input(over):
+    """The merged weights written over the base or over a delta, where the single read would come back to its
+    inputs: k = n (sums beyond the binary32 bound, every tile merged again), a misleading sample and record areas
+    full of ties (two passes), and a tensor that needs neither.  Bit-exact with the oracle."""
+    rng = np.random.default_rng(130)
+    K, n = 2, 1024 * 4096
+    blk = (np.arange(n) // 256) % 4 == 0
+    bad = Unit(1024, 4096, nm.from_f64(rng.standard_normal(n) * 0.02, "bf16"),
+               [nm.from_f64(rng.standard_normal(n) * np.where(blk, 1e-6, 1e-2), "bf16") for _ in range(K)], "bf16", n // 10)
+    few = Unit(256, 1000, nm.from_f64(rng.standard_normal(256000) * 0.02, "bf16"),
+               [nm.from_f64(rng.integers(-5, 6, 256000) * 2.0 ** -12, "bf16") for _ in range(K)], "bf16", 76800)
+    units = [normal_unit(rng, 300, 301, K, k=300 * 301), bad, few, normal_unit(rng, 1024, 1023, K)]
+    es = [u.entry() for u in units]
+    for e in es:
+        e.out = e.base if over == "base" else e.deltas[0]
+    ws = iso.workspace(iso.OP_UPDATE_FUSED_SELECT, es, K, iso.BF16)
+    say(f"fused, weights written over the {over}")
+    iso.iso_update(es, K, iso.BF16, iso.UPDATE_FUSED, merge=iso.MERGE_TIES, lam=1.0, desc=None, ws=ws)
+    assert iso.iso_read_device_status(ws) == 0
+    check(units, K, [from_dev(e.out, u.n, "bf16") for e, u in zip(es, units)], None)
