@@ -116,7 +116,12 @@ __global__ void k_fs_init(const DevTensor* __restrict__ tab, int n_t, int K, Fus
   const int64_t k = (g < 0) ? T.k : G.gk[g];
   FusedUnit f;
   f.flags = (k == 0) ? kFusedNone : ((k == ((g < 0) ? T.n : G.gn[g])) ? kFusedAll : 0u);
-  if (f.flags & kFusedNone) f.lo = f.hi = f.prov = 0x8000u;   // above every key: nothing kept
+  // k == 0: 0x8000 lies above every key, nothing is kept.  Calls with joint selections flag a non-finite delta
+  // also there: such keys alone are kept provisionally, so their tiles are merged again and checked.
+  if (f.flags & kFusedNone) {
+    f.lo = f.hi = 0x8000u;
+    f.prov = (G.gid != nullptr) ? 0x7F80u : 0x8000u;
+  }
   else f.lo = f.hi = f.prov = 0u;                            // k == n: every nonzero key is above
   f.t_key = 0;
   f.share = 0;
@@ -430,7 +435,7 @@ __device__ __forceinline__ uint32_t wave_scan_u32(uint32_t x) {
 
 // Provisional threshold of a delta in the main pass: kept iff key >= prov_key.
 __device__ __forceinline__ uint32_t prov_key(const FusedUnit& F) {
-  return (F.flags & kFusedNone) ? 0x8000u : max(F.prov, 1u);
+  return max(F.prov, 1u);
 }
 
 // One pair of coordinates (word h of the K deltas' vectors w and of the base wb): provisional

@@ -269,3 +269,21 @@ def test_joint_single_read_of_many_units():
     iso.iso_update(es, K, iso.BF16, iso.UPDATE_FUSED, merge=iso.MERGE_TIES, desc=None, ws=ws)
     assert iso.iso_read_device_status(ws) == 0 and iso.iso_read_fallback_count(ws) == 0
     assert torch.equal(out.view(torch.int16), want.view(torch.int16))
+
+
+def test_non_finite_delta_of_a_group_that_keeps_nothing():
+    """A joint call flags a non-finite delta whatever its selection keeps: in a group with a count of 0, and in a lone
+    tensor with k = 0 beside it, below and above the size from which one read is taken."""
+    import torch
+    for rows in (64, 8192):
+        for bad in (None, 0, 1):
+            case = dict(K=2, fill=_randn(1e-4), shapes=[(rows, 8192, 1, 0), (64, 512, 0, 0), (64, 512, 2, 5000)])
+            es, _, out, _, _ = _flat_group_call(case)
+            if bad is not None:
+                es[bad].deltas[1][77] = float("inf")
+            ws = iso.workspace(iso.OP_UPDATE_FUSED_SELECT, es, 2, iso.BF16)
+            say(f"joint, nothing kept, {rows} rows, infinity in {bad}")
+            iso.iso_update(es, 2, iso.BF16, iso.UPDATE_FUSED, merge=iso.MERGE_TIES, desc=None, ws=ws)
+            assert (iso.iso_read_device_status(ws) != 0) == (bad is not None), (rows, bad)
+            if bad is None:
+                assert torch.equal(es[0].out, es[0].base) and torch.equal(es[1].out, es[1].base)
