@@ -469,8 +469,9 @@ iso_status iso_read_fallback_count(const void* ws, void* stream, int32_t* count)
  * milliseconds and the number of regions timed; the library keeps its events for reuse.
  * Calls on several host threads at once are timed too, in no particular order.
  * iso_profile_flops returns the binary64 flops the timed polar iterations performed since
- * iso_profile_begin: per job (frame side of rows x rank, m x q) and step taken, 2 m q^2 for
- * the Gram X^T X (formed whole) and 2 m q^2 for the product X T (0 for the merge paths). */
+ * iso_profile_begin: per job (frame side of rows x rank, m x q) and step taken, 2 m for each
+ * entry of the Gram X^T X that is computed (its square tiles on or above the diagonal; the
+ * others are their mirror) and 2 m q^2 for the product X T (0 for the merge paths). */
 iso_status iso_profile_begin(void);
 iso_status iso_profile_end(double* total_ms, int32_t* launches);
 iso_status iso_profile_flops(double* flops);

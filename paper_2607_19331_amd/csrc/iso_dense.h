@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "iso_device.h"
+#include "iso_gemm_job.h"
 
 namespace iso {
 namespace {
@@ -1023,23 +1024,6 @@ constexpr int GK = 16;
 namespace iso {
 namespace {
 
-// A batch of independent GEMMs in one launch: grid.z indexes the job; blocks outside a
-// job's M x N exit.  C(i,j) = alpha * sum_k A(i,k) B(k,j) + beta * C(i,j) with X(i,k) at
-// X[i*xs0 + k*xs1].  `upper`: only the tiles on or above the diagonal are computed, for a
-// symmetric product; 1: the caller fills in the lower triangle where it needs one, 2: a tile above
-// the diagonal is also stored transposed below it.  `skip`: if set and *skip is nonzero when the
-// kernel runs, the job is left out (an iteration whose job has converged).
-struct GemmJob {
-  const double* A;
-  const double* B;
-  double* C;
-  int64_t as0, as1, bs0, bs1, cs0, cs1;
-  int64_t M, N, K;
-  double alpha, beta;
-  int upper;
-  const int* skip;
-};
-
 typedef double gemm_f64x4_t __attribute__((ext_vector_type(4)));
 typedef double gemm_f64x2_t __attribute__((ext_vector_type(2)));
 typedef double gemm_f64x2_u __attribute__((ext_vector_type(2), aligned(8)));   // 16 bytes at 8-byte alignment
@@ -1221,17 +1205,6 @@ __device__ __forceinline__ void gemm_tile_of(int t, int gx, int gy, bool upper, 
   by = j0 + t % wd;
 }
 
-// Tiles gemm_tile_of numbers (for `upper` a few of them lie below the diagonal).
-__host__ __device__ __forceinline__ int gemm_tiles(int gx, int gy, bool upper) {
-  if (!upper) return gx * gy;
-  int n = 0;
-  for (int j0 = 0; j0 < gy; j0 += 4) {
-    const int wd = (gy - j0 < 4) ? gy - j0 : 4;
-    n += ((gx < j0 + wd) ? gx : j0 + wd) * wd;
-  }
-  return n;
-}
-
 template <int W>
 __device__ __forceinline__ void gemm_tile(const GemmJob& J) {
   using T = GemmTile<W>;
@@ -1277,17 +1250,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
 template <int W>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_gemm_one(GemmJob J) {
   gemm_tile<W>(J);
-}
-
-// Tile side for n products of M x N outputs: the largest of 128, 64 and 32 that still gives every
-// CU a workgroup and computes at most a quarter more padding than the next smaller one.  With fewer
-// workgroups than CUs the chip idles and one tile's serial k loop sets the time.
-inline int gemm_side(int64_t M, int64_t N, int64_t n) {
-  const int64_t cus = 256;
-  auto tiles = [&](int64_t side) { return ((M + side - 1) / side) * ((N + side - 1) / side); };
-  for (int side = 128; side > 32; side /= 2)
-    if (tiles(side) * n >= cus && 16 * tiles(side) <= 5 * tiles(side / 2)) return side;
-  return 32;
 }
 
 inline unsigned gemm_grid(int64_t M, int64_t N, int side, bool upper) {

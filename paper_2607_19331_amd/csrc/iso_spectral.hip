@@ -1105,7 +1105,7 @@ iso_status run_spectral(const iso_tensor* t, int n_t, int K, iso_dtype dt, const
 
 // polar_batch over the frames' 2 n_f jobs (frame e's U side at 2 e, V side at 2 e + 1) inside a
 // profiling region, counting the binary64 flops its steps performed: per job of m x q and step
-// taken, 2 m q^2 for the Gram (formed whole) and 2 m q^2 for the product.
+// taken, 2 m per entry of the Gram that is computed (one triangle of tiles) and 2 m q^2 for the product.
 hipError_t timed_polar(const Tables& tb, const iso_frame* f, int n_f, int64_t max_rows, int64_t max_q,
                        std::vector<NsState>& hst, uint32_t* status, hipStream_t s, bool scaled) {
   hipEvent_t ev[2];
@@ -1116,9 +1116,10 @@ hipError_t timed_polar(const Tables& tb, const iso_frame* f, int n_f, int64_t ma
   if (ev[1] != nullptr && (e = hipEventRecord(ev[1], s)) != hipSuccess) return e;
   if (ev[0] != nullptr) {
     double flops = 0.0;
+    const int side = gemm_side(max_q, max_q, 2 * n_f);          // of the batch's Gram products
     for (int j = 0; j < 2 * n_f; ++j) {
       const double m = (double)((j & 1) ? f[j / 2].cols : f[j / 2].rows), q = (double)f[j / 2].rank;
-      flops += (double)hst[j].steps * (4.0 * m * q * q);
+      flops += (double)hst[j].steps * 2.0 * m * ((double)gemm_upper_entries(f[j / 2].rank, side) + q * q);
     }
     profile_add_flops(flops);
   }

@@ -163,9 +163,9 @@ def test_muon_zero_and_ill_conditioned_directions():
         flops = iso.iso_profile_flops()
         ms, regions = iso.iso_profile_end()
         assert iso.iso_read_device_status(ws) == 0
-        # two timed polar iterations (directions, retraction), every job at least one step of
-        # 4 m q^2 flops in each
-        unit = sum(4.0 * r * q * q for _, m, n, q in specs for r in (m, n))
+        # two timed polar iterations (directions, retraction), every job at least one step in each: at least
+        # half the Gram's entries and the product, 3 m q^2 flops
+        unit = sum(3.0 * r * q * q for _, m, n, q in specs for r in (m, n))
         assert regions == 2 and ms > 0.0 and flops >= 2 * unit
         for (kind, *_), F, R in zip(specs, frames, ref):
             R["u"], R["v"], w_ref, R["st"] = op.iso_muon_step(R["u"], R["v"], R["s"], R["g"], R["st"], hp["lr"],
@@ -214,3 +214,26 @@ def test_product_tile_edges(shapes):
         assert np.abs(_back(F.v, F.cols, F.rank) - v).max() <= 1e-10
         got, ref = from_dev(F.w_out, F.rows * F.cols, "f32").astype(np.float64), w.ravel()
         assert np.max(np.abs(got - ref) / np.maximum(np.abs(ref), 2.0 ** -10 * np.abs(ref).max())) <= 1e-6
+
+
+def test_profile_flops_count_the_grams_computed_entries():
+    """256 x 256 frames of full rank: the Grams' 32-wide tiles on or above the diagonal are 36 of 64, so one
+    Newton-Schulz step of a job is 2 * 256 * (36 * 32^2 + 256^2) flops, and the counter a whole number of them."""
+    import torch
+    rng = np.random.default_rng(43)
+    m = n = q = 256
+    u, _ = np.linalg.qr(rng.standard_normal((m, q)))
+    v, _ = np.linalg.qr(rng.standard_normal((n, q)))
+    z = [_colmajor(np.zeros((r, q))) for r in (m, m, n, n)]
+    F = iso.Frame(rows=m, cols=n, rank=q, u=_colmajor(u), v=_colmajor(v), sigma=torch.linspace(2.0, 0.5, q, dtype=torch.float64, device="cuda"),
+                  m_u=z[0], v_u=z[1], m_v=z[2], v_v=z[3], grad=to_dev(nm.from_f64(rng.standard_normal(m * n) * 0.1, "f32")),
+                  w_out=torch.empty(m * n, dtype=torch.int32, device="cuda"))
+    ws = iso.optimizer_workspace([F])
+    say("iso-adamw flop counter")
+    iso.iso_profile_begin()
+    iso.iso_optimizer_step([F], iso.F32, step=1, lr=1e-3, ws=ws)
+    flops = iso.iso_profile_flops()
+    iso.iso_profile_end()
+    assert iso.iso_read_device_status(ws) == 0
+    steps = flops / (2.0 * 256 * (36 * 32 * 32 + 256 * 256))
+    assert steps == int(steps) and 2 <= steps <= 96, steps
