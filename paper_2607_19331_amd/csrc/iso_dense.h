@@ -1048,7 +1048,7 @@ typedef double gemm_f64x2_u __attribute__((ext_vector_type(2), aligned(8)));   /
 // read whole cache lines, and staged in the layout that load writes without bank conflicts:
 // k-major ([k][i], rows of PAD doubles) for an operand read along i, i-major ([i][k], rows of
 // SK = GK + 2 doubles) for one read along k; the rows of a fragment read then fall on different
-// banks in either layout.  One of each operand's strides has to be 1.
+// banks in either layout.  One of each operand's strides has to be 1 (gemm_job_ok).
 template <int W>
 struct GemmTile {
   static constexpr int TM = 32 * W, TW = 16 * W, PAD = (W == 2) ? 80 : TM + 16, PT = GK * TM / 512;
@@ -1257,7 +1257,8 @@ inline unsigned gemm_grid(int64_t M, int64_t N, int side, bool upper) {
   return (unsigned)(8 * std::max(1, (t + 7) / 8));
 }
 
-// njobs jobs from a device table, at most max_m x max_n outputs each (upper: all of them `upper`).
+// njobs jobs from a device table, at most max_m x max_n outputs each (upper: all of them `upper`).  Who
+// builds the table checks it (gemm_table_ok).
 inline void gemm_jobs(const GemmJob* jobs, int njobs, int64_t max_m, int64_t max_n, hipStream_t s, bool upper = false) {
   const int side = gemm_side(max_m, max_n, njobs);
   const dim3 g(gemm_grid(max_m, max_n, side, upper), 1, (unsigned)njobs);
@@ -1266,20 +1267,23 @@ inline void gemm_jobs(const GemmJob* jobs, int njobs, int64_t max_m, int64_t max
   else k_gemm_jobs<1><<<g, 256, 0, s>>>(jobs);
 }
 
-// One job with every field given (a sub-block product, the `upper` tiles).
-inline void gemm_job(const GemmJob& J, hipStream_t s) {
+// One job with every field given (a sub-block product, the `upper` tiles); a form that the kernels do not take
+// is refused.
+[[nodiscard]] inline hipError_t gemm_job(const GemmJob& J, hipStream_t s) {
+  if (!gemm_job_ok(J)) return hipErrorInvalidValue;
   const int side = gemm_side(J.M, J.N, 1);
   const unsigned g = gemm_grid(J.M, J.N, side, J.upper != 0);
   if (side == 128) k_gemm_one<4><<<g, 256, 0, s>>>(J);
   else if (side == 64) k_gemm_one<2><<<g, 256, 0, s>>>(J);
   else k_gemm_one<1><<<g, 256, 0, s>>>(J);
+  return hipSuccess;
 }
 
 // C(i,j) = alpha * sum_k A(i,k) B(k,j) + beta * C(i,j); X(i,k) at X[i*xs0 + k*xs1].
-inline void gemm(int64_t M, int64_t N, int64_t Kd, double alpha, const double* A, int64_t as0, int64_t as1,
+[[nodiscard]] inline hipError_t gemm(int64_t M, int64_t N, int64_t Kd, double alpha, const double* A, int64_t as0, int64_t as1,
                  const double* B, int64_t bs0, int64_t bs1, double beta, double* C, int64_t cs0, int64_t cs1,
                  hipStream_t s) {
-  gemm_job(GemmJob{A, B, C, as0, as1, bs0, bs1, cs0, cs1, M, N, Kd, alpha, beta, 0, nullptr}, s);
+  return gemm_job(GemmJob{A, B, C, as0, as1, bs0, bs1, cs0, cs1, M, N, Kd, alpha, beta, 0, nullptr}, s);
 }
 
 // ---- Cholesky factor of a symmetric positive definite matrix ------------------------------------

@@ -23,6 +23,21 @@ struct GemmJob {
   const int* skip;
 };
 
+// The forms that the kernels take: each operand has a stride of 1 (they read 16 bytes along it), and in a launch
+// whose grid numbers one triangle of tiles (`upper`) every job is `upper`.  They do not check it: a job of
+// another form would give wrong numbers.  A job without outputs is left out by them.
+inline bool gemm_job_ok(const GemmJob& J, bool upper = false) {
+  if (J.M <= 0 || J.N <= 0) return true;
+  return (J.as0 == 1 || J.as1 == 1) && (J.bs0 == 1 || J.bs1 == 1) && (!upper || J.upper != 0);
+}
+
+// n jobs of a host table.
+inline bool gemm_table_ok(const GemmJob* jobs, int64_t n, bool upper = false) {
+  for (int64_t j = 0; j < n; ++j)
+    if (!gemm_job_ok(jobs[j], upper)) return false;
+  return true;
+}
+
 // Tiles gemm_tile_of numbers (for `upper` a few of them lie below the diagonal).
 constexpr int gemm_tiles(int gx, int gy, bool upper) {
   if (!upper) return gx * gy;

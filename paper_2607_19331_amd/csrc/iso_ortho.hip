@@ -216,13 +216,13 @@ void om_norms(const double* x, int64_t stride, int64_t len, int nv, double* part
 }
 
 // C = A B^T for n x n col-major matrices
-void gemm_abt(int64_t n, const double* A, const double* B, double* C, hipStream_t s) {
-  gemm(n, n, n, 1.0, A, 1, n, B, n, 1, 0.0, C, 1, n, s);
+hipError_t gemm_abt(int64_t n, const double* A, const double* B, double* C, hipStream_t s) {
+  return gemm(n, n, n, 1.0, A, 1, n, B, n, 1, 0.0, C, 1, n, s);
 }
 
 // C = A B for n x n col-major matrices
-void gemm_ab(int64_t n, const double* A, const double* B, double* C, hipStream_t s) {
-  gemm(n, n, n, 1.0, A, 1, n, B, 1, n, 0.0, C, 1, n, s);
+hipError_t gemm_ab(int64_t n, const double* A, const double* B, double* C, hipStream_t s) {
+  return gemm(n, n, n, 1.0, A, 1, n, B, 1, n, 0.0, C, 1, n, s);
 }
 
 // Job tables of a batch of nm matrices: the nm K jobs of the Procrustes and inverse-Cayley job
@@ -341,7 +341,7 @@ iso_status run_ortho(const iso_tensor* t, int n_t, int K, iso_dtype dt, double l
       k_om_load<<<gmn, 256, 0, s>>>(b.w0, x.base, nullptr, m, n, dt);
       for (int i = 0; i < K; ++i) {
         k_om_load<<<gmn, 256, 0, s>>>(b.wi[i], x.base, x.deltas[i], m, n, dt);
-        gemm(n, n, m, 1.0, b.w0, m, 1, b.wi[i], 1, m, 0.0, b.ja[i], 1, n, s);
+        OM_TRY(gemm(n, n, m, 1.0, b.w0, m, 1, b.wi[i], 1, m, 0.0, b.ja[i], 1, n, s));
       }
     }
     // 2. R_i = U V^T from the SVDs of M_i, every matrix's K SVDs as one job set
@@ -352,7 +352,7 @@ iso_status run_ortho(const iso_tensor* t, int n_t, int K, iso_dtype dt, double l
       const int64_t n = t[ids[e]].cols;
       for (int i = 0; i < K; ++i) {
         k_om_check_min<<<1, 64, 0, s>>>(b.S[i], n, status);
-        gemm_abt(n, b.U[i], b.V[i], b.R[i], s);
+        OM_TRY(gemm_abt(n, b.U[i], b.V[i], b.R[i], s));
         // 3. the SPD matrix 2I + R + R^T into the Jacobi matrix, R - R^T into A_i
         k_om_sym_skew<<<grid_for(n * n), 256, 0, s>>>(b.ja[i], b.A[i], b.R[i], n);
       }
@@ -365,9 +365,9 @@ iso_status run_ortho(const iso_tensor* t, int n_t, int K, iso_dtype dt, double l
       const int64_t n = t[ids[e]].cols;
       const unsigned gnn = grid_for(n * n);
       for (int i = 0; i < K; ++i) {
-        gemm(n, n, n, 1.0, b.U[i], n, 1, b.A[i], 1, n, 0.0, b.T, 1, n, s);     // T = U^T D
+        OM_TRY(gemm(n, n, n, 1.0, b.U[i], n, 1, b.A[i], 1, n, 0.0, b.T, 1, n, s));     // T = U^T D
         k_om_div_cols<<<gnn, 256, 0, s>>>(b.V[i], b.V[i], b.S[i], n, n, status);
-        gemm_ab(n, b.V[i], b.T, b.A[i], s);                                      // A_i = V S^{-1} T
+        OM_TRY(gemm_ab(n, b.V[i], b.T, b.A[i], s));                                      // A_i = V S^{-1} T
       }
       // 4. A = (mean |A_i|) sum A_i / |sum A_i|
       for (int i = 0; i < K; ++i) om_norms(b.A[i], 0, n * n, 1, b.part, b.norm + i, s);
@@ -377,7 +377,7 @@ iso_status run_ortho(const iso_tensor* t, int n_t, int K, iso_dtype dt, double l
       k_om_coef<<<1, 64, 0, s>>>(b.norm, K, b.coef);
       k_om_scale<<<gnn, 256, 0, s>>>(b.asum, b.coef, n * n);
       // 5. I - A^2 into the Jacobi matrix, I + A into P
-      gemm_ab(n, b.asum, b.asum, b.T, s);
+      OM_TRY(gemm_ab(n, b.asum, b.asum, b.T, s));
       k_om_forward_parts<<<gnn, 256, 0, s>>>(b.ja[0], b.P, b.T, b.asum, n);
     }
     // 5. R = (I + A)^2 (I - A^2)^{-1}, W_rot = W_0 R
@@ -388,13 +388,13 @@ iso_status run_ortho(const iso_tensor* t, int n_t, int K, iso_dtype dt, double l
       const OmBufs& b = bs[e];
       const int64_t m = x.rows, n = x.cols;
       k_om_div_cols<<<grid_for(n * n), 256, 0, s>>>(b.V[0], b.V[0], b.S[0], n, n, status);
-      gemm_abt(n, b.V[0], b.U[0], b.T, s);                                     // (I - A^2)^{-1}
-      gemm_ab(n, b.P, b.P, b.PP, s);
-      gemm_ab(n, b.PP, b.T, b.Rm, s);
-      gemm(m, n, n, 1.0, b.w0, 1, m, b.Rm, 1, n, 0.0, b.wrot, 1, m, s);
+      OM_TRY(gemm_abt(n, b.V[0], b.U[0], b.T, s));                                     // (I - A^2)^{-1}
+      OM_TRY(gemm_ab(n, b.P, b.P, b.PP, s));
+      OM_TRY(gemm_ab(n, b.PP, b.T, b.Rm, s));
+      OM_TRY(gemm(m, n, n, 1.0, b.w0, 1, m, b.Rm, 1, n, 0.0, b.wrot, 1, m, s));
       // 6. residuals delta_i = W_i - W_0 R_i (binary32, row-major) and their TIES merge
       for (int i = 0; i < K; ++i) {
-        gemm(m, n, n, -1.0, b.w0, 1, m, b.R[i], 1, n, 1.0, b.wi[i], 1, m, s);
+        OM_TRY(gemm(m, n, n, -1.0, b.w0, 1, m, b.R[i], 1, n, 1.0, b.wi[i], 1, m, s));
         k_om_to_f32<<<grid_for(m * n), 256, 0, s>>>(b.delta[i], b.wi[i], m, n);
       }
       OM_TRY(hipGetLastError());

@@ -528,19 +528,22 @@ std::vector<std::vector<int>> spectral_batches(const iso_tensor* t, int n_t, int
 }
 
 // xi = D - U0 sym(U0^T D) in place on D (r x q col-major), using P, S (q x q) as scratch
-void tangent_project(double* d, const double* u0, int64_t r, int64_t q, double* P, double* S, hipStream_t s) {
-  gemm(q, q, r, 1.0, u0, r, 1, d, 1, r, 0.0, P, 1, q, s);           // P = U0^T D
+hipError_t tangent_project(double* d, const double* u0, int64_t r, int64_t q, double* P, double* S, hipStream_t s) {
+  hipError_t e;
+  if ((e = gemm(q, q, r, 1.0, u0, r, 1, d, 1, r, 0.0, P, 1, q, s)) != hipSuccess) return e;           // P = U0^T D
   k_sym<<<grid_for(q * q), 256, 0, s>>>(S, P, q);
-  gemm(r, q, q, -1.0, u0, 1, r, S, 1, q, 1.0, d, 1, r, s);          // D -= U0 S
+  if ((e = gemm(r, q, q, -1.0, u0, 1, r, S, 1, q, 1.0, d, 1, r, s)) != hipSuccess) return e;          // D -= U0 S
+  return hipSuccess;
 }
 
 // Steps 2 - 6 up to the polar inputs for one matrix whose K+1 SVDs are final: canonicalisation,
 // tangent projections, D_keep, effect proxies, Gram, ridge solve and clip, aggregate projection;
 // leaves U_0 + xi_U* in AU and V_0 + xi_V* in AV.
-void middle_steps(const Bufs& b, int64_t m, int64_t n, int K, const SpectralArgs& a, double* coef_out,
-                  uint32_t* status, hipStream_t s) {
+hipError_t middle_steps(const Bufs& b, int64_t m, int64_t n, int K, const SpectralArgs& a, double* coef_out,
+                        uint32_t* status, hipStream_t s) {
   const int64_t q = std::min(m, n);
   const int64_t keep = std::min<int64_t>(q, (int64_t)std::floor(a.rho_keep * (double)q + 0.5));
+  hipError_t e;
   for (int i = 1; i <= K; ++i) {
     double* xu = b.XU + (int64_t)(i - 1) * m * q;
     double* xv = b.XV + (int64_t)(i - 1) * n * q;
@@ -549,16 +552,16 @@ void middle_steps(const Bufs& b, int64_t m, int64_t n, int K, const SpectralArgs
     // 3. displacements, tangent projection, D_keep
     k_sub<<<grid_for(m * q), 256, 0, s>>>(xu, b.U[i], b.U[0], m * q);
     k_sub<<<grid_for(n * q), 256, 0, s>>>(xv, b.V[i], b.V[0], n * q);
-    tangent_project(xu, b.U[0], m, q, b.P, b.Sq, s);
-    tangent_project(xv, b.V[0], n, q, b.P, b.Sq, s);
+    if ((e = tangent_project(xu, b.U[0], m, q, b.P, b.Sq, s)) != hipSuccess) return e;
+    if ((e = tangent_project(xv, b.V[0], n, q, b.P, b.Sq, s)) != hipSuccess) return e;
     k_mask_cols<<<grid_for(m * q), 256, 0, s>>>(xu, m, q, keep);
     k_mask_cols<<<grid_for(n * q), 256, 0, s>>>(xv, n, q, keep);
     // 4. g_i = xi_U Sigma_0 V_0^T + U_0 Sigma_0 xi_V^T  (m x n col-major)
     double* g = b.G + (int64_t)(i - 1) * m * n;
     k_scale_cols<<<grid_for(m * q), 256, 0, s>>>(b.FU, xu, b.S[0], m, q);
-    gemm(m, n, q, 1.0, b.FU, 1, m, b.V[0], n, 1, 0.0, g, 1, m, s);
+    if ((e = gemm(m, n, q, 1.0, b.FU, 1, m, b.V[0], n, 1, 0.0, g, 1, m, s)) != hipSuccess) return e;
     k_scale_cols<<<grid_for(m * q), 256, 0, s>>>(b.FU, b.U[0], b.S[0], m, q);
-    gemm(m, n, q, 1.0, b.FU, 1, m, xv, n, 1, 1.0, g, 1, m, s);
+    if ((e = gemm(m, n, q, 1.0, b.FU, 1, m, xv, n, 1, 1.0, g, 1, m, s)) != hipSuccess) return e;
   }
   // 5. Gram, ridge solve, clip
   gram_of(b.G, m * n, K, b.red, b.gram, s);
@@ -566,10 +569,11 @@ void middle_steps(const Bufs& b, int64_t m, int64_t n, int K, const SpectralArgs
   // 6. aggregate, project, shift to the base factors
   k_combine<<<grid_for(m * q), 256, 0, s>>>(b.AU, b.XU, b.coef, K, m * q);
   k_combine<<<grid_for(n * q), 256, 0, s>>>(b.AV, b.XV, b.coef, K, n * q);
-  tangent_project(b.AU, b.U[0], m, q, b.P, b.Sq, s);
-  tangent_project(b.AV, b.V[0], n, q, b.P, b.Sq, s);
+  if ((e = tangent_project(b.AU, b.U[0], m, q, b.P, b.Sq, s)) != hipSuccess) return e;
+  if ((e = tangent_project(b.AV, b.V[0], n, q, b.P, b.Sq, s)) != hipSuccess) return e;
   k_add<<<grid_for(m * q), 256, 0, s>>>(b.AU, b.AU, b.U[0], m * q);
   k_add<<<grid_for(n * q), 256, 0, s>>>(b.AV, b.AV, b.V[0], n * q);
+  return hipSuccess;
 }
 
 // Newton-Schulz polar over the batch's 2 nm jobs (X of job p in buffer 0 on entry); the host
@@ -731,6 +735,11 @@ iso_status run_batch(const iso_tensor* t, const std::vector<int>& ids, int K, is
     svd_r = std::max(svd_r, jr_rows);
     svd_c = std::max(svd_c, q);
   }
+  for (int k = 0; k < 4; ++k)
+    if (!gemm_table_ok(hg[k], npol, k % 2 == 0)) return ISO_ERR_INTERNAL;
+  for (int k = 0; k < 5; ++k)
+    if (!gemm_table_ok(hq[k], npol, true)) return ISO_ERR_INTERNAL;
+  if (!gemm_table_ok(hw, nm * K)) return ISO_ERR_INTERNAL;
   SP_TRY(hipMemcpyAsync(ws, host.data(), tables_end, hipMemcpyHostToDevice, s));
   // 1. W_0 and W_i = W_0 + tau_i as A = W (tall) or W^T (wide), r x q col-major; SVDs.  When the
   //    batch's Jacobi workgroups outnumber what the chip holds at once, the base goes first and
@@ -770,7 +779,7 @@ iso_status run_batch(const iso_tensor* t, const std::vector<int>& ids, int K, is
       const int64_t q = std::min(x.rows, x.cols), r = std::max(x.rows, x.cols);
       const Bufs& b = bs[e];
       for (int i = 0; i <= K; ++i)
-        gemm_job(GemmJob{b.ja[i], b.ja[i], b.jr[i], r, 1, 1, r, 1, q, q, q, r, 1.0, 0.0, 1, nullptr}, se);
+        SP_TRY(gemm_job(GemmJob{b.ja[i], b.ja[i], b.jr[i], r, 1, 1, r, 1, q, q, q, r, 1.0, 0.0, 1, nullptr}, se));
     }
     SP_TRY(fan.end());
   }
@@ -822,7 +831,7 @@ iso_status run_batch(const iso_tensor* t, const std::vector<int>& ids, int K, is
       for (int i = 0; i <= K; ++i) {
         double* L = wide ? b.V[i] : b.U[i];
         const double* Vs = wide ? b.U[i] : b.V[i];
-        gemm(r, q, q, 1.0, b.ja[i], 1, r, Vs, 1, q, 0.0, L, 1, r, se);
+        SP_TRY(gemm(r, q, q, 1.0, b.ja[i], 1, r, Vs, 1, q, 0.0, L, 1, r, se));
         k_unit_cols<<<grid_for(r * q), 256, 0, se>>>(L, b.S[i], r, q);
       }
     }
@@ -871,7 +880,7 @@ iso_status run_batch(const iso_tensor* t, const std::vector<int>& ids, int K, is
       const int64_t m = t[ids[e]].rows, n = t[ids[e]].cols, q = std::min(m, n);
       const Bufs& b = bs[e];
       hipStream_t se = fan.at(e);
-      middle_steps(b, m, n, K, a, a.coef_out ? a.coef_out + (int64_t)ids[e] * K : nullptr, status, se);
+      SP_TRY(middle_steps(b, m, n, K, a, a.coef_out ? a.coef_out + (int64_t)ids[e] * K : nullptr, status, se));
       k_copy<<<grid_for(m * q), 256, 0, se>>>(b.PX[0][0], b.AU, m * q);
       k_copy<<<grid_for(n * q), 256, 0, se>>>(b.PX[1][0], b.AV, n * q);
     }
@@ -893,7 +902,7 @@ iso_status run_batch(const iso_tensor* t, const std::vector<int>& ids, int K, is
       const int h = m > n ? 0 : 1;
       const int64_t rows = h ? n : m;
       const Bufs& b = bs[e];
-      gemm(rows, q, q, 1.0, b.PX[h][0], 1, rows, b.QP[hsq[2 * e + h].steps & 1], 1, q, 0.0, b.PX[h][1], 1, rows, s);
+      SP_TRY(gemm(rows, q, q, 1.0, b.PX[h][0], 1, rows, b.QP[hsq[2 * e + h].steps & 1], 1, q, 0.0, b.PX[h][1], 1, rows, s));
     }
   }
   {
@@ -909,7 +918,7 @@ iso_status run_batch(const iso_tensor* t, const std::vector<int>& ids, int K, is
       hipStream_t se = fan.at(e);
       // 7. W_* = U_* Sigma_0 V_*^T
       k_scale_cols<<<grid_for(m * q), 256, 0, se>>>(b.FU, Us, b.S[0], m, q);
-      gemm(m, n, q, 1.0, b.FU, 1, m, Vs, n, 1, 0.0, b.Wst, 1, m, se);
+      SP_TRY(gemm(m, n, q, 1.0, b.FU, 1, m, Vs, n, 1, 0.0, b.Wst, 1, m, se));
       k_store_w<<<grid_for(m * n), 256, 0, se>>>(x.out, b.Wst, m, n, dt, status);
     }
     SP_TRY(fan.end());
@@ -1170,6 +1179,8 @@ iso_status run_optimizer(const iso_frame* f, int n_f, iso_dtype dt, const iso_ad
     max_rows = std::max(max_rows, std::max(m, n));
     max_q = std::max(max_q, q);
   }
+  for (int k = 0; k < 4; ++k)
+    if (!gemm_table_ok(hg[k], 2 * n_f, k % 2 == 0)) return ISO_ERR_INTERNAL;
   OP_TRY(hipMemcpyAsync(ws, host.data(), tables_end, hipMemcpyHostToDevice, s));
   const double bc1 = adam ? 1.0 - std::pow(adam->beta1, (double)adam->step) : 1.0;
   const double bc2 = adam ? 1.0 - std::pow(adam->beta2, (double)adam->step) : 1.0;
@@ -1181,8 +1192,8 @@ iso_status run_optimizer(const iso_frame* f, int n_f, iso_dtype dt, const iso_ad
     k_load_f64<<<grid_for(m * n), 256, 0, s>>>(b.G, F.grad, nullptr, m, n, 0, dt);
     k_scale_cols<<<grid_for(n * q), 256, 0, s>>>(b.FV, F.v, F.sigma, n, q);
     k_scale_cols<<<grid_for(m * q), 256, 0, s>>>(b.FU, F.u, F.sigma, m, q);
-    gemm(m, q, n, 1.0, b.G, 1, m, b.FV, 1, n, 0.0, b.GU, 1, m, s);
-    gemm(n, q, m, 1.0, b.G, m, 1, b.FU, 1, m, 0.0, b.GV, 1, n, s);
+    OP_TRY(gemm(m, q, n, 1.0, b.G, 1, m, b.FV, 1, n, 0.0, b.GU, 1, m, s));
+    OP_TRY(gemm(n, q, m, 1.0, b.G, m, 1, b.FU, 1, m, 0.0, b.GV, 1, n, s));
     if (adam) {
       // AdamW on the frames (in place), then the tentative frames go to the iterate buffers
       k_adamw<<<grid_for(m * q), 256, 0, s>>>(F.u, b.GU, F.m_u, F.v_u, m * q, adam->lr, adam->beta1, adam->beta2,
@@ -1227,7 +1238,7 @@ iso_status run_optimizer(const iso_frame* f, int n_f, iso_dtype dt, const iso_ad
     k_copy<<<grid_for(m * q), 256, 0, s>>>(F.u, Us, m * q);
     k_copy<<<grid_for(n * q), 256, 0, s>>>(F.v, Vs, n * q);
     k_scale_cols<<<grid_for(m * q), 256, 0, s>>>(b.FU, Us, F.sigma, m, q);
-    gemm(m, n, q, 1.0, b.FU, 1, m, Vs, n, 1, 0.0, b.Wst, 1, m, s);
+    OP_TRY(gemm(m, n, q, 1.0, b.FU, 1, m, Vs, n, 1, 0.0, b.Wst, 1, m, s));
     k_store_w<<<grid_for(m * n), 256, 0, s>>>(F.w_out, b.Wst, m, n, dt, status);
   }
   OP_TRY(hipGetLastError());
@@ -1273,7 +1284,7 @@ iso_status run_spectrum_ops(const iso_tensor* t, int n_t, iso_dtype dt, Spectrum
       const double* lf = wide ? b.V[0] : b.U[0];     // r x q left factor of A
       const double* rf = wide ? b.U[0] : b.V[0];     // q x q right factor
       k_scale_cols<<<grid_for(r * q), 256, 0, s>>>(b.G, lf, b.S[0], r, q);
-      gemm(r, q, q, 1.0, b.G, 1, r, rf, q, 1, 0.0, b.ja[1], 1, r, s);
+      SO_TRY(gemm(r, q, q, 1.0, b.G, 1, r, rf, q, 1, 0.0, b.ja[1], 1, r, s));
       SO_TRY(jacobi_block(tb.jobs + 1, 1, r, q, tb.jst + 1, status, s, false, split));
       svd_finalize(tb.jobs + 1, tb.ptrs + 1, tb.ptrs + 3, tb.ptrs + 5, 1, q, s);
       k_spectral_error<<<1, 1024, 0, s>>>(b.S[0], b.S[1], q, out + j);
@@ -1295,7 +1306,7 @@ iso_status run_spectrum_ops(const iso_tensor* t, int n_t, iso_dtype dt, Spectrum
       // Delta W and W_0 col-major, P = Delta W V_0
       k_load_f64<<<grid_for(m * n), 256, 0, s>>>(b.G, t[j].deltas[0], nullptr, m, n, 0, dt);
       k_load_f64<<<grid_for(m * n), 256, 0, s>>>(b.Wst, t[j].base, nullptr, m, n, 0, dt);
-      gemm(m, q, n, 1.0, b.G, 1, m, b.V[0], 1, n, 0.0, b.FU, 1, m, s);
+      SO_TRY(gemm(m, q, n, 1.0, b.G, 1, m, b.V[0], 1, n, 0.0, b.FU, 1, m, s));
       k_col_dot_sq<<<(unsigned)std::min<int64_t>((q + 15) / 16, 4096), 1024, 0, s>>>(b.U[0], b.FU, m, q, b.P);
       dot1(b.Wst, b.Wst, m * n, false, b.red, b.gram, s);
       dot1(b.G, b.G, m * n, false, b.red, b.gram + 1, s);
@@ -1303,7 +1314,7 @@ iso_status run_spectrum_ops(const iso_tensor* t, int n_t, iso_dtype dt, Spectrum
     } else if (op == SpectrumOp::kInterpolate) {
       k_mix<<<grid_for(q), 256, 0, s>>>(b.P, b.S[0], b.S[1], q, param);
       k_scale_cols<<<grid_for(m * q), 256, 0, s>>>(b.FU, b.U[1], b.P, m, q);
-      gemm(m, n, q, 1.0, b.FU, 1, m, b.V[1], n, 1, 0.0, b.Wst, 1, m, s);
+      SO_TRY(gemm(m, n, q, 1.0, b.FU, 1, m, b.V[1], n, 1, 0.0, b.Wst, 1, m, s));
       k_store_w<<<grid_for(m * n), 256, 0, s>>>(t[j].out, b.Wst, m, n, dt, status);
     } else {
       // Prop. 3.1 with W_j = base (factors 0) and W_i = base + delta (factors 1), all col-major, at
@@ -1314,22 +1325,22 @@ iso_status run_spectrum_ops(const iso_tensor* t, int n_t, iso_dtype dt, Spectrum
         double* wi = b.ja[0];
         double* wj = b.ja[1];
         k_scale_cols<<<grid_for(m * rk), 256, 0, s>>>(b.FU, b.U[1], b.S[1], m, rk);
-        gemm(m, n, rk, 1.0, b.FU, 1, m, b.V[1], n, 1, 0.0, wi, 1, m, s);
+        SO_TRY(gemm(m, n, rk, 1.0, b.FU, 1, m, b.V[1], n, 1, 0.0, wi, 1, m, s));
         k_scale_cols<<<grid_for(m * rk), 256, 0, s>>>(b.FU, b.U[0], b.S[0], m, rk);
-        gemm(m, n, rk, 1.0, b.FU, 1, m, b.V[0], n, 1, 0.0, wj, 1, m, s);
+        SO_TRY(gemm(m, n, rk, 1.0, b.FU, 1, m, b.V[0], n, 1, 0.0, wj, 1, m, s));
         dot1(wi, wj, m * n, true, b.red, o, s);
         // T1 = U_j^T W_i^(r) (rk x n), W_L = U_j T1
-        gemm(rk, n, m, 1.0, b.U[0], m, 1, wi, 1, m, 0.0, b.FV, 1, rk, s);
-        gemm(m, n, rk, 1.0, b.U[0], 1, m, b.FV, 1, rk, 0.0, b.G, 1, m, s);
+        SO_TRY(gemm(rk, n, m, 1.0, b.U[0], m, 1, wi, 1, m, 0.0, b.FV, 1, rk, s));
+        SO_TRY(gemm(m, n, rk, 1.0, b.U[0], 1, m, b.FV, 1, rk, 0.0, b.G, 1, m, s));
         dot1(wi, b.G, m * n, true, b.red, o + 2, s);
         // T2 = W_i^(r) V_j (m x rk), W_R = T2 V_j^T
-        gemm(m, rk, n, 1.0, wi, 1, m, b.V[0], 1, n, 0.0, b.XU, 1, m, s);
-        gemm(m, n, rk, 1.0, b.XU, 1, m, b.V[0], n, 1, 0.0, b.G, 1, m, s);
+        SO_TRY(gemm(m, rk, n, 1.0, wi, 1, m, b.V[0], 1, n, 0.0, b.XU, 1, m, s));
+        SO_TRY(gemm(m, n, rk, 1.0, b.XU, 1, m, b.V[0], n, 1, 0.0, b.G, 1, m, s));
         dot1(wi, b.G, m * n, true, b.red, o + 3, s);
         // core B = T1 V_j (rk x rk), W_mix = (U_j B) V_j^T
-        gemm(rk, rk, n, 1.0, b.FV, 1, rk, b.V[0], 1, n, 0.0, b.P, 1, rk, s);
-        gemm(m, rk, rk, 1.0, b.U[0], 1, m, b.P, 1, rk, 0.0, b.AU, 1, m, s);
-        gemm(m, n, rk, 1.0, b.AU, 1, m, b.V[0], n, 1, 0.0, b.G, 1, m, s);
+        SO_TRY(gemm(rk, rk, n, 1.0, b.FV, 1, rk, b.V[0], 1, n, 0.0, b.P, 1, rk, s));
+        SO_TRY(gemm(m, rk, rk, 1.0, b.U[0], 1, m, b.P, 1, rk, 0.0, b.AU, 1, m, s));
+        SO_TRY(gemm(m, n, rk, 1.0, b.AU, 1, m, b.V[0], n, 1, 0.0, b.G, 1, m, s));
         dot1(wi, b.G, m * n, true, b.red, o + 1, s);
         k_transport_final<<<1, 64, 0, s>>>(b.S[0], b.S[1], q, rk, o);
       }

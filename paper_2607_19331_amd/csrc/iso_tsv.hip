@@ -1337,6 +1337,8 @@ iso_status run_tsv(const iso_tensor* t, int n_t, int K, const TsvArgs& a, uint8_
       gj[5].push_back(GemmJob{M.U, M.MU, M.Up, M.ldk, 1, M.Kr, 1, M.Kr, 1, M.R, M.Kr, M.Kr, 1.0, 0.0});
       gj[5].push_back(GemmJob{M.V, M.MV, M.Vp, M.ldk, 1, M.Kr, 1, M.Kr, 1, M.C, M.Kr, M.Kr, 1.0, 0.0});
     }
+    for (int q = 0; q < 12; ++q)
+      if (!gemm_table_ok(gj[q].data(), (int64_t)gj[q].size())) return ISO_ERR_INTERNAL;
     // upload tables (one staging buffer, kept until the chunk is done)
     const size_t tb = table_bytes(nm, K);
     host.assign(tb, 0);
