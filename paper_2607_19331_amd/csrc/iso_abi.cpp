@@ -436,8 +436,9 @@ size_t iso_workspace_size(int op, const iso_tensor* t, int n_t, int K, int dt) {
   for (int j = 0; j < n_t; ++j)
     if (t[j].rows < 0 || t[j].cols < 0) return 0;
   if (op == ISO_OP_BLOCKDIAG) return 0;
+  const Layout L = plan(op, t, n_t, K, dt);
   // with joint selections either path may run (see iso_update)
-  return std::max(plan(op, t, n_t, K, dt).total, plan(op, t, n_t, K, dt, false).total);
+  return (L.fused && L.n_groups > 0) ? std::max(L.total, plan(op, t, n_t, K, dt, false).total) : L.total;
 }
 
 iso_status iso_topk_mask(const iso_tensor* t, int n_t, int K, int dt, iso_select_desc* desc,

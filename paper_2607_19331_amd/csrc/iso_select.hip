@@ -10,6 +10,8 @@
 // unit) then finds the digit holding the k-th largest key.  If only part of the
 // threshold bucket is kept, a tie pass counts threshold keys per 64K-element
 // chunk and a find kernel walks to the quota-th tie in flat order.
+#include <vector>
+
 #include "iso_device.h"
 #include "iso_kernels.h"
 
@@ -903,18 +905,28 @@ int64_t hist_chunk_for(const iso_tensor* t, int n_t, int K, int dt, bool fallbac
   int64_t c0 = 1 << 16;
   while (c0 < most && total / c0 > 2048) c0 <<= 1;
   if (fallback || c0 == most) return c0;
+  // A tensor of at most c0 entries is one item per delta whatever the chunk; the others, at most 2048 / K, are
+  // counted for each.  (All tensors for each of up to 33 chunks: 53 us for 339 tensors, 3.6 ms for 20000, on the host.)
+  std::vector<int64_t> large;
+  int64_t ones = 0;
+  for (int j = 0; j < n_t; ++j) {
+    const int64_t n = t[j].rows * t[j].cols;
+    if (n > c0) large.push_back(n);
+    else if (n > 0) ++ones;
+  }
   const int64_t overhead = (dt == ISO_BF16) ? 1 << 16 : 1 << 15;
   int64_t best = c0, best_cost = INT64_MAX;
   for (int64_t oct = c0; oct <= most; oct *= 2)
     for (int64_t c = oct; c < 2 * oct && c <= most; c += oct / 8) {
-      int64_t items = 0;
-      for (int j = 0; j < n_t; ++j) items += K * ((t[j].rows * t[j].cols + c - 1) / c);
+      int64_t items = K * ones;
+      for (const int64_t n : large) items += K * ((n + c - 1) / c);
       const int64_t cost = (items + 255) / 256 * (c + overhead);
       if (cost < best_cost) {
         best = c;
         best_cost = cost;
       }
       if (items <= 256) return best;             // a larger chunk only lengthens the one wave
+      if (large.empty()) return best;            // nor does it save an item
     }
   return best;
 }

@@ -308,3 +308,22 @@ def test_profile_flops_counter_without_a_gpu():
     iso.iso_profile_begin()
     assert iso.iso_profile_flops() == 0.0
     assert iso.iso_profile_end() == (0.0, 0)
+
+
+def test_planning_a_selection_of_many_small_tensors_is_cheap():
+    """Every call plans its workspace on the host.  For 20000 small tensors a selection's plan (the histogram chunk
+    among its rules) costs a few times one without a selection, which walks the table as well; a rule that counts
+    all tensors' items for each of its chunks costs 25 to 40 times."""
+    import time
+    es = [iso.Entry(8, 64, k=1) for _ in range(20000)]
+    L, tab = _lib.load(), iso._table(es)
+
+    def best(op):
+        took = []
+        for _ in range(9):
+            t0 = time.perf_counter()
+            assert L.iso_workspace_size(op, tab, len(es), 4, iso.F32) > 0
+            took.append(time.perf_counter() - t0)
+        return min(took)
+
+    assert best(iso.OP_TOPK) < 12 * best(iso.OP_MERGE)
