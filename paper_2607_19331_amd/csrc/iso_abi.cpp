@@ -144,10 +144,12 @@ bool fused_eligible(int op, int n_t, int dt) {
 }
 
 // Joint selections take it from this many coordinates in the call.  The two-pass path's launches cost
-// less below (K = 8: 2^21 coordinates 120 against 175 us, 2^24 240 against 240); at 2^26 one read
-// takes K = 1: 144 against 185 us, K = 2: 179 / 234, K = 4: 260 / 349, K = 8: 457 / 568, at 2^27 four
-// deltas 393 against 576.  A group of few distinct magnitudes is given up after its sample and then
-// costs 70 to 170 us more than two passes alone, which the line keeps a small share.
+// less below (K = 8: 2^21 coordinates 120 against 175 us, 2^24 240 against 240); at 2^26 one read of
+// Gaussian deltas takes K = 1: 145 against 184 us, K = 2: 179 / 235, K = 4: 261 / 348, K = 8: 456 / 568, at
+// 2^27 four deltas 392 against 577.  A group of few distinct magnitudes (differences of bf16 weights) is given
+// up after its sample and takes longer than two passes alone, 60 to 130 us up to 2^28: at 2^26 in one member
+// K = 1: 269 against 210 us, K = 2: 353 / 292, K = 4: 511 / 447, K = 8: 816 / 756, in 56 members 297 / 220,
+// 412 / 328, 589 / 500, 970 / 877; at 2^28 K = 1: 657 / 569, K = 4: 1494 / 1407.
 constexpr int64_t kFusedGroupMin = 1ll << 26;
 
 // Whether a merged weight may be written over an input of its tensor.  The two-pass merge reads an

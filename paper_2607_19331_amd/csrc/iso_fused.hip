@@ -1351,7 +1351,10 @@ hipError_t launch_k(const FusedPlan& pl, hipStream_t s) {
   if (e != hipSuccess) return e;
   MergePlan mp = pl.mrg;
   mp.filter = pl.tflag;
-  if (pl.grp.n_groups > 0) mp.flagged_grid = 4096;   // joint selections: large calls, whose groups go together
+  if (pl.grp.n_groups > 0) {                     // joint selections: large calls, whose groups go together
+    mp.tmap = pl.tmap;
+    mp.flagged = sp.flagged;
+  }
   mp.desc = sp.desc;
   mp.prof[0] = mp.prof[1] = nullptr;
   return run_merge(mp, ISO_BF16, s);

@@ -69,9 +69,9 @@ struct MergePlan {
   int64_t tiles;                // total tiles over the table
   uint32_t* status;
   const int* filter = nullptr;  // n_t device flags: only flagged tensors are merged; null: every tensor
-  // Workgroups with a filter.  4096 instead of 1024 merge a flagged group of 2^27 coordinates (two deltas, one
-  // member) in 562 instead of 595 us a call, and cost a call that flags nothing 2 us.
-  unsigned flagged_grid = 1024;
+  const uint32_t* flagged = nullptr;   // with tmap: how many tensors are flagged
+  const int* tmap = nullptr;    // with a filter: the call's coarse tile map (find_tensor_mapped) where whole groups
+                                // are flagged and the tiles are walked in runs; null: scattered over 1024 workgroups
   hipEvent_t prof[2] = {nullptr, nullptr};   // recorded around the merge kernel when set
 };
 

@@ -272,6 +272,35 @@ __global__ void __launch_bounds__(kMergeThreads) k_merge_flagged(const DevTensor
       });
 }
 
+// Tiles per workgroup of k_merge_flagged_runs.  A wave that goes on to another tile waits for its last stores
+// together with its next loads (one counter), so long runs are slow where tensors are flagged; where none is, a
+// workgroup that leaves at once still costs the call 0.2 to 0.3 ns.  2^31 coordinates in one group, a whole call,
+// against 4096 workgroups that share the tiles out one by one (128 each): flagged K = 1 4492 -> 4150 us (runs of 4:
+// 4227), K = 2 6896 -> 6445, K = 4 11527 -> 10924 (runs of 16: 11111), K = 8 20669 -> 20097; not flagged K = 1
+// 2408 -> 2479, K = 2 3314 -> 3342, K = 4 5215 -> 5222, K = 8 9776 -> 9734.
+constexpr int flagged_run(int K) { return (K == 1) ? 2 : 4; }
+
+// Flagged groups (most or all of the call, unlike single tensors): each workgroup takes a run of neighbouring tiles
+// of the whole call and leaves out what is not flagged.  flagged: the number of flagged tensors.
+template <int DT, int K, int MODE, int OUTS, int VPT>
+__global__ void __launch_bounds__(kMergeThreads) k_merge_flagged_runs(const DevTensor* __restrict__ tab,
+                                                                      const int* __restrict__ tmap, int n_t,
+                                                                      const iso_select_desc* __restrict__ desc,
+                                                                      double lambda, double eps, uint32_t* status,
+                                                                      const int* __restrict__ filter,
+                                                                      const uint32_t* __restrict__ flagged,
+                                                                      int64_t tiles) {
+  if (*flagged == 0u) return;
+  int64_t tile = (int64_t)blockIdx.x * flagged_run(K);
+  const int64_t end = min(tiles, tile + flagged_run(K));
+  for (int j = find_tensor_mapped(tab, tmap, n_t, tile); tile < end; ++j) {
+    const int64_t last = (j + 1 < n_t) ? min(end, tab[j + 1].tile0) : end;    // tensors without entries: no tile
+    if (filter[j])
+      for (; tile < last; ++tile) merge_tile<DT, K, MODE, OUTS, VPT>(tab, n_t, desc, lambda, eps, status, tile);
+    tile = last;
+  }
+}
+
 // ---- APPLY: out = round(w0 + lambda * tau_in) ----------------------------------------------------
 
 template <int DT>
@@ -339,8 +368,16 @@ __global__ void __launch_bounds__(kMergeThreads) k_apply(const DevTensor* __rest
 template <int DT, int K, int MODE, int OUTS>
 static void launch_merge(const MergePlan& pl, hipStream_t s) {
   if (pl.filter != nullptr) {
-    k_merge_flagged<DT, K, MODE, OUTS, kMergeVPT><<<pl.flagged_grid, kMergeThreads, 0, s>>>(
-        pl.tab, pl.n_t, pl.desc, pl.lambda, pl.eps, pl.status, pl.filter);
+    // the single-read path's fallback: bf16 TIES weights, with or without signs
+    if constexpr (DT == ISO_BF16 && MODE == ISO_MERGE_TIES && (OUTS & OUT_W) != 0)
+      if (pl.tmap != nullptr) {
+        k_merge_flagged_runs<DT, K, MODE, OUTS, kMergeVPT>
+            <<<(unsigned)((pl.tiles + flagged_run(K) - 1) / flagged_run(K)), kMergeThreads, 0, s>>>(
+                pl.tab, pl.tmap, pl.n_t, pl.desc, pl.lambda, pl.eps, pl.status, pl.filter, pl.flagged, pl.tiles);
+        return;
+      }
+    k_merge_flagged<DT, K, MODE, OUTS, kMergeVPT><<<1024, kMergeThreads, 0, s>>>(pl.tab, pl.n_t, pl.desc, pl.lambda,
+                                                                               pl.eps, pl.status, pl.filter);
     return;
   }
   const int64_t grid = (kMergeMaxGrid > 0) ? std::min(pl.tiles, kMergeMaxGrid) : pl.tiles;

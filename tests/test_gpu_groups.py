@@ -192,6 +192,9 @@ def _late_run(n, g):
 
 BIG = (8192, 8192)                                   # 2^26 entries, from which the single read is taken: 2^18 blocks,
 ALONE = (*BIG, 0, 3000000)                           # of which 2^12 are sampled; alone, or as a member
+# a flagged group of a large tensor, an empty one and 30 of one to four tiles, each beside one of a group that is not
+LATE_AND_SMALL = [(*BIG, 1, int(0.2025 * (1 << 26)))] + [(1 + j % 3, 4093 + j % 7, 1 + j % 2, j % 2 * 1000) for j in range(60)] + \
+                 [(0, 9, 1, 0), (1024, 1024, 2, 200000)]
 JOINT = dict(
     ragged=dict(K=4, fill=_randn(1e-4), shapes=[(1537, 2053, 1, 300000), (0, 7, 1, 0), ALONE, (13, 17, 2, 30), (1, 255, 1, 99),
                                                 (700, 1999, 2, 90000), (511, 1025, 0, 20000), (1001, 1003, 1, 0)]),
@@ -201,6 +204,8 @@ JOINT = dict(
                                                               ALONE]),
     records_full_in_main_pass=dict(K=2, fill=_late_run, two_pass=2, shapes=[(*BIG, 1, int(0.2025 * (1 << 26))), (1000, 1000, 2, 0),
                                                                             (512, 512, 1, 0), (1024, 1024, 2, 300000)]),
+    one_delta_flagged_beside_unflagged=dict(K=1, fill=_late_run, two_pass=32, shapes=LATE_AND_SMALL),
+    five_deltas_flagged_beside_unflagged=dict(K=5, fill=_late_run, two_pass=32, shapes=LATE_AND_SMALL),
     missed_bracket=dict(K=2, fill=_odd_blocks_large, shapes=[(*BIG, 1, 200000), (1024, 4096, 2, 300000)]),
     all_kept=dict(K=2, fill=_randn(1e-3), shapes=[(*BIG, 1, 8192 * 8192 + 999), (27, 37, 1, 0), (1024, 1024, 2, 0)]),
     eight_experts=dict(K=8, fill=_randn(5e-5), shapes=[(*BIG, 1, 10000000), (900, 901, 1, 90000), (1000, 1100, 1, 1)]),
