@@ -207,10 +207,10 @@ JOINT = dict(
     one_delta_flagged_beside_unflagged=dict(K=1, fill=_late_run, two_pass=32, shapes=LATE_AND_SMALL),
     five_deltas_flagged_beside_unflagged=dict(K=5, fill=_late_run, two_pass=32, shapes=LATE_AND_SMALL),
     missed_bracket=dict(K=2, fill=_odd_blocks_large, shapes=[(*BIG, 1, 200000), (1024, 4096, 2, 300000)]),
-    all_kept=dict(K=2, fill=_randn(1e-3), shapes=[(*BIG, 1, 8192 * 8192 + 999), (27, 37, 1, 0), (1024, 1024, 2, 0)]),
+    all_kept=dict(K=2, fill=_randn(1e-3), two_pass=2, shapes=[(*BIG, 1, 8192 * 8192 + 999), (27, 37, 1, 0), (1024, 1024, 2, 0)]),
     eight_experts=dict(K=8, fill=_randn(5e-5), shapes=[(*BIG, 1, 10000000), (900, 901, 1, 90000), (1000, 1100, 1, 1)]),
-    zeros_kept=dict(K=2, fill=lambda n, g: _randn(1e-4)(n, g) * (_randn(1.0)(n, g) > 1.0),
-                    shapes=[(*BIG, 1, 50000000), (500, 777, 1, 300000)]),
+    zeros_kept=dict(K=2, fill=lambda n, g: _randn(1e-4)(n, g) * (_randn(1.0)(n, g) > 1.0), two_pass=3,
+                    shapes=[(*BIG, 1, 50000000), (500, 777, 1, 300000), (600, 500, 0, 290000), (600, 500, 0, 30000)]),
 )
 
 
