@@ -61,10 +61,10 @@ def test_tie_cutoff_inside_chunks(dtype):
     check(units, 2, dtype)
 
 
-@pytest.mark.parametrize("copies", [1, 30])
+@pytest.mark.parametrize("copies", [1, 40])
 def test_sample_of_few_and_of_many_deltas(copies):
     """iso_update FUSED TIES around the size up to which a delta is histogrammed whole (2^20), with a few deltas
-    (each sample split over several workgroups) and with more than there are CUs (one workgroup each)."""
+    (20: each sample split over 12 workgroups) and with more than there are CUs (332: one workgroup each)."""
     rng = np.random.default_rng(73)
     units = []
     for n in (1, 9, 4097, (1 << 20) - 1, 1 << 20, (1 << 20) + 257):
