@@ -648,7 +648,6 @@ def main():
     if whole:
         for e in entries:
             e.group = 1
-        args.path = "two-pass"
     single = args.path == "single-read"
     if single:
         ws_upd = iso.workspace(iso.OP_UPDATE_FUSED_SELECT, entries, K, iso.BF16, dev)

@@ -1205,18 +1205,26 @@ __device__ __forceinline__ void gemm_tile_of(int t, int gx, int gy, bool upper, 
   by = j0 + t % wd;
 }
 
+// Tiles per job from which the XCDs take runs of them, over a grid padded to a multiple of 8.  Below, one workgroup
+// per tile in plain order: the padding would be up to seven eighths of the grid, always on the same XCDs (168
+// products of 256^3, four tiles each: 238 us with the tiles on four XCDs, 157 on all; 1344 products of 256 x 256 x 1184
+// or less 4.2 against 2.3 ms; the TSV of a whole 7B model 132.2 against 125.4 ms).
+constexpr unsigned kGemmRunsFrom = 16;
+
 template <int W>
 __device__ __forceinline__ void gemm_tile(const GemmJob& J) {
   using T = GemmTile<W>;
   __shared__ __attribute__((aligned(16))) double As[2][T::BUF];
   __shared__ __attribute__((aligned(16))) double Bs[2][T::BUF];
   if (J.M <= 0 || J.N <= 0) return;
-  // workgroups go to the eight XCDs in turn (gridDim.x is a multiple of 8): each takes a run of
-  // consecutive tiles
   const int gx = (int)((J.M + T::TM - 1) / T::TM), gy = (int)((J.N + T::TM - 1) / T::TM);
-  const int nt = gemm_tiles(gx, gy, J.upper != 0), per = (nt + 7) / 8;
-  const int slot = blockIdx.x >> 3, t = (blockIdx.x & 7) * per + slot;
-  if (slot >= per || t >= nt) return;
+  const int nt = gemm_tiles(gx, gy, J.upper != 0);
+  // from kGemmRunsFrom on workgroups go to the eight XCDs in turn (gridDim.x is a multiple of 8): each takes a
+  // run of consecutive tiles
+  const int per = (nt + 7) / 8, slot = blockIdx.x >> 3;
+  const bool runs = gridDim.x >= kGemmRunsFrom;
+  const int t = runs ? (int)(blockIdx.x & 7) * per + slot : (int)blockIdx.x;
+  if ((runs && slot >= per) || t >= nt) return;
   if (J.skip != nullptr && *J.skip != 0) return;
   int bx, by;
   gemm_tile_of(t, gx, gy, J.upper != 0, bx, by);
@@ -1253,8 +1261,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
 }
 
 inline unsigned gemm_grid(int64_t M, int64_t N, int side, bool upper) {
-  const int t = gemm_tiles((int)((M + side - 1) / side), (int)((N + side - 1) / side), upper);
-  return (unsigned)(8 * std::max(1, (t + 7) / 8));
+  const unsigned t = (unsigned)gemm_tiles((int)((M + side - 1) / side), (int)((N + side - 1) / side), upper);
+  return (t < kGemmRunsFrom) ? std::max(1u, t) : (t + 7) / 8 * 8;
 }
 
 // njobs jobs from a device table, at most max_m x max_n outputs each (upper: all of them `upper`).  Who

@@ -21,8 +21,9 @@
 // codes or a full record region sends the tensor to the exact two-pass path (histogram
 // select, then merge) on the same stream; the result is identical either way.  Tensors selected
 // jointly share one sample and one bracket per delta, their counts are added before the resolve, the
-// tie quota goes to the members in table order, and one member on the two-pass path takes its group.  Zero keys
-// need no decision: a kept zero adds nothing to the election or to the mean.
+// tie quota goes to the members in table order, and one member on the two-pass path takes its group.  The sample
+// gives up groups whose records or sums would not fit before the main pass reads them.  Zero keys need no decision:
+// a kept zero adds nothing to the election or to the mean.
 #include <algorithm>
 
 #include "iso_device.h"

@@ -185,7 +185,8 @@ def test_muon_zero_and_ill_conditioned_directions():
     [(1, 1, 1), (31, 33, 31), (65, 32, 17), (15, 130, 15)],      # 32-wide product tiles, k shorter than one step
     [(1025, 1030, 1023)],                                        # 64-wide tiles, one row past, one column short
     [(513, 516, 513)] * 8,                                       # 128-wide tiles in the batched products
-], ids=["tile32", "tile64", "tile128"])
+    [(256, 129, 129)] + [(256, 256, 256)] * 40,                  # the same, four tiles a job and fewer
+], ids=["tile32", "tile64", "tile128", "four_tiles"])
 def test_product_tile_edges(shapes):
     """One ISO-AdamW step at the edges of the product tiles (each tile side is chosen by how many tiles the
     outputs make): gradients, both polar factors' Gram (one triangle and its mirror) and step products, W+.
