@@ -564,7 +564,7 @@ def main():
                          "general binary64 rounding path of the fused pass)")
     ap.add_argument("--select", default="per-tensor", choices=["per-tensor", "whole-model"],
                     help="whole-model: one TopKMask over the concatenation of every tensor's delta (all "
-                         "tensors in one select_group; the two-pass path)")
+                         "tensors in one select_group)")
     ap.add_argument("--rule", default="adamw", choices=["adamw", "muon"],
                     help="base rule of the ISO-Optimizer step (--config layer-optimizer)")
     ap.add_argument("--no-cpu-baseline", action="store_true")

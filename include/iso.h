@@ -159,6 +159,9 @@ typedef struct iso_select_desc {
 /*
  * Bytes of workspace the given operation needs for this table (0 on bad
  * arguments).  ISO_OP_BLOCKDIAG also needs the rank: use iso_workspace_size_tsv.
+ * ISO_OP_UPDATE_FUSED_SELECT with select groups and at least 2^26 coordinates:
+ * about 1 byte per coordinate (4 for K > 4) more than the size for ISO_OP_TOPK,
+ * for the single read; the call also takes the latter and then makes two passes.
  */
 size_t iso_workspace_size(int op, const iso_tensor* t, int n_t, int K, int dt);
 
@@ -264,9 +267,10 @@ iso_status iso_update(const iso_tensor* t, int n_t, int K, int dt, const iso_upd
  * that forbid hipMalloc).  Same arguments, modes and results as iso_update;
  * the workspace is a fixed block of ISO_NOALLOC_SCRATCH_BYTES of static device
  * memory per GPU, which the library holds until the process ends.  The call
- * allocates nothing.  A call whose workspace (iso_workspace_size of its mode)
- * exceeds the block is rejected with ISO_ERR_UNSUPPORTED before anything is
- * queued; 64 MiB covers, e.g., a fused TopKMask + TIES update of one tensor of
+ * allocates nothing.  A call whose workspace (iso_workspace_size of its mode; for
+ * FUSED TIES with select groups that of ISO_OP_TOPK, see there) exceeds the
+ * block is rejected with ISO_ERR_UNSUPPORTED before anything is queued;
+ * 64 MiB covers, e.g., a fused TopKMask + TIES update of one tensor of
  * about 6M bf16 entries with K = 4.
  * scratch_out (nullable) receives the device address of the current device's
  * block: pass it as the workspace of iso_read_device_status and
