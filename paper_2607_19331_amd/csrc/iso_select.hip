@@ -894,9 +894,11 @@ __global__ void k_fill_u32(uint32_t* p, int64_t n, uint32_t v) {
 
 // Entries per histogram work item.  At most 2048 items, in chunks of 2^16 to 2^20 entries, is the
 // coarse rule (and the only one where the histogram is the single-read path's fallback).  A CU runs
-// one item at a time, and an item costs about as much as 2^16 bf16 (2^15 fp32) entries besides its
-// entries (clearing, flush and dump of its bins), so among the larger chunks the one with the least
-// waves * (entries + overhead) is taken.  12 deltas of 4.2M to 8.4M bf16 entries: 1028 items of 2^16
+// one item at a time, and an item costs about as much as 2^16 bf16 entries besides its entries (clearing,
+// flush and dump of its bins; 3 * 2^13 fp32 entries, the mean of one pass over all bins and two over few), so among
+// the larger chunks the one with the least waves * (entries + overhead) is taken.  The CUs do not end long fp32
+// items together: c^2 / 2^22 is added for the last wave (in one wave of 655360 entries 143M fp32 entries took 464 us,
+// in three of 212992 393; 32M in one wave of 147456 120 us, in two of 65536 140).  12 deltas of 4.2M to 8.4M bf16 entries: 1028 items of 2^16
 // in five waves -> 252 items in one, the select and what follows it 268 -> 235 us.
 int64_t hist_chunk_for(const iso_tensor* t, int n_t, int K, int dt, bool fallback) {
   int64_t total = 0;
@@ -914,13 +916,13 @@ int64_t hist_chunk_for(const iso_tensor* t, int n_t, int K, int dt, bool fallbac
     if (n > c0) large.push_back(n);
     else if (n > 0) ++ones;
   }
-  const int64_t overhead = (dt == ISO_BF16) ? 1 << 16 : 1 << 15;
+  const int64_t overhead = (dt == ISO_BF16) ? 1 << 16 : 3 << 13;
   int64_t best = c0, best_cost = INT64_MAX;
   for (int64_t oct = c0; oct <= most; oct *= 2)
     for (int64_t c = oct; c < 2 * oct && c <= most; c += oct / 8) {
       int64_t items = K * ones;
       for (const int64_t n : large) items += K * ((n + c - 1) / c);
-      const int64_t cost = (items + 255) / 256 * (c + overhead);
+      const int64_t cost = (items + 255) / 256 * (c + overhead) + (dt == ISO_BF16 ? 0 : c * c >> 22);
       if (cost < best_cost) {
         best = c;
         best_cost = cost;
